@@ -24,11 +24,12 @@ bool aligned256(const void* p) { return ((uintptr_t)p & 255u) == 0; }
 // Layout change with stage timing; with H, the one-DM chirp table (of dm),
 // and with delays the channel delays, are built by the same kernel.
 int launch_transposed(const BeamPlan& p, const void* in, void* out, void* stream,
-                      void* H = nullptr, double dm = 0.0, int32_t* delays = nullptr) {
+                      void* H = nullptr, double dm = 0.0, int32_t* delays = nullptr,
+                      int variant = 0) {
   void* tok = nullptr;
   int e = stage_begin(kStageTranspose, stream, &tok);
   if (e) return e;
-  if ((e = H ? launch_transpose_chirp(p, in, out, dm, H, stream, delays)
+  if ((e = H ? launch_transpose_chirp(p, in, out, dm, H, stream, delays, variant)
              : launch_transpose(in, out, p.dtype, p.nsamp, p.nchan, xt_stride(p), stream)))
     return e;
   return stage_end(kStageTranspose, stream, tok);
@@ -63,7 +64,7 @@ cdd_status run_tile(const BeamPlan& p, const void* voltages, const DmTile& tile,
       table_built = table && transpose_chirp_fits(p);
       if ((e = begin(kStageTranspose)) ||
           (e = table_built ? launch_transpose_chirp(p, voltages, ws + lay.xt_off, tile.dm[0], H,
-                                                    stream, d)
+                                                    stream, d, p.variant)
                            : launch_transpose(voltages, ws + lay.xt_off, p.dtype, p.nsamp,
                                               p.nchan, xt_stride(p), stream)) ||
           (e = end(kStageTranspose)))
@@ -83,7 +84,7 @@ cdd_status run_tile(const BeamPlan& p, const void* voltages, const DmTile& tile,
   if (!table_built) {
     if ((e = begin(kStageDelays))) return device_fail("event record", e);
     if (!direct && (e = launch_delays(p, tile, d, stream))) return device_fail("delay launch", e);
-    if (table && (e = launch_chirp_table(p, tile.dm[0], H, stream)))
+    if (table && (e = launch_chirp_table(p, tile.dm[0], H, stream, p.variant)))
       return device_fail("chirp table launch", e);
     if ((e = end(kStageDelays))) return device_fail("event record", e);
   }
@@ -653,6 +654,8 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
     // later beams beside the transforms of earlier ones slows both down on
     // this GPU as much as it hides); the single-launch form changes every
     // layout first.
+    // (the single-launch form runs the default schedule of each length)
+    auto variant_of = [&](size_t b) { return plan->single_launch ? 0 : plan->beams[b].variant; };
     auto fused = [&](size_t b) { return H[b] && transpose_chirp_fits(plan->beams[b]); };
     auto d_of = [&](size_t b) { return (int32_t*)(ws + plan->ws_base[b] + plan->lay[b].d_off); };
     bool use_aux = false;
@@ -672,7 +675,7 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
       int err = 0;
       void* tok = nullptr;
       if ((err = stage_begin(kStageDelays, aux.aux, &tok)) ||
-          (H[b] && (err = launch_chirp_table(p, p.dms[0], H[b], aux.aux))) ||
+          (H[b] && (err = launch_chirp_table(p, p.dms[0], H[b], aux.aux, variant_of(b)))) ||
           (err = launch_delays(p, t0, d_of(b), aux.aux)) ||
           (err = stage_end(kStageDelays, aux.aux, tok)))
         st = device_fail("chirp table or delay launch", err);
@@ -684,7 +687,7 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
       if (p.nchan > 1 &&
           (err = launch_transposed(p, plan->desc[b].voltages, (void*)xt[b], stream,
                                    fused(b) ? H[b] : nullptr, p.dms[0],
-                                   fused(b) ? d_of(b) : nullptr))) {
+                                   fused(b) ? d_of(b) : nullptr, variant_of(b)))) {
         st = device_fail("transpose launch", err);
         break;
       }

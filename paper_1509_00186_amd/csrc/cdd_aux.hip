@@ -161,7 +161,7 @@ bool transpose_chirp_fits(const BeamPlan& p) {
 }
 
 int launch_transpose_chirp(const BeamPlan& p, const void* in, void* out, double dm, void* H,
-                           void* stream, int32_t* delays) {
+                           void* stream, int32_t* delays, int variant) {
   if (!transpose_chirp_fits(p) || H == nullptr) return (int)hipErrorInvalidValue;
   const int64_t tiles_c = (p.nchan + 127) / 128, tiles_t = (p.nsamp + 63) / 64;
   const int64_t n = tiles_c * tiles_t;
@@ -169,7 +169,7 @@ int launch_transpose_chirp(const BeamPlan& p, const void* in, void* out, double 
   // the fewest table entries per thread that the layout change's workgroups cover
   int kpt = 1;
   while ((int64_t)p.nchan * (p.N / (256 * kpt)) > n && 256 * kpt * 2 <= p.N) kpt *= 2;
-  const ChirpTableArgs ct = chirp_table_args(p, dm, H, kpt);
+  const ChirpTableArgs ct = chirp_table_args(p, dm, H, kpt, variant);
   DelayArgs dl{};
   if (delays) {
     dl.d = delays;

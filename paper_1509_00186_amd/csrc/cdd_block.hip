@@ -84,6 +84,7 @@ struct BlockArgs {
   int32_t nchan, M, nfront, n_int, dtype, phase_mode, exact_div, taper;
   int32_t accum;        // add to P instead of storing (second polarisation)
   int32_t lgn;          // log2 N (mixed launches switch on it)
+  float gain;           // DM tiles: relative correction of the transforms' gain (gain_of)
   double f_lo, df, dconst;
   double dm_step;       // DM tiles: dms.dm[i] = dms.dm[0] + i dm_step, or 0 if not so spaced
   DmTile dms;
@@ -201,32 +202,6 @@ __device__ __forceinline__ void apply_chirp_dm(float2* v, double dm, const doubl
   (void)N;
 }
 
-// exp(-2 pi i x) for |x| <= 1/2 turn, rounded to FP32: the quadrant
-// n = rint(4x) is taken out exactly, and the sine and cosine of the remaining
-// angle (at most pi/4) come from their Taylor series in FP64 through the
-// 11th and 12th powers (truncation below 1e-11, far under FP32 rounding).
-__device__ __forceinline__ float2 expi_neg_turns_fp64(double x) {
-  const double n = rint(4.0 * x);
-  const double th = 6.283185307179586 * fma(n, -0.25, x);
-  const double t2 = th * th;
-  double sp = fma(t2, -2.505210838544172e-08, 2.755731922398589e-06);  // 1/11!, 1/9!
-  sp = fma(t2, sp, -1.984126984126984e-04);                            // 1/7!
-  sp = fma(t2, sp, 8.333333333333333e-03);                             // 1/5!
-  sp = fma(t2, sp, -1.666666666666667e-01);                            // 1/3!
-  const double sv = fma(th * t2, sp, th);
-  double cp = fma(t2, 2.087675698786810e-09, -2.755731922398589e-07);  // 1/12!, 1/10!
-  cp = fma(t2, cp, 2.480158730158730e-05);                             // 1/8!
-  cp = fma(t2, cp, -1.388888888888889e-03);                            // 1/6!
-  cp = fma(t2, cp, 4.166666666666667e-02);                             // 1/4!
-  cp = fma(t2, cp, -0.5);
-  const double cv = fma(t2, cp, 1.0);
-  // rotate by the quadrant: exp(2 pi i x) = i^n exp(i th)
-  const int q = ((int)n) & 3;
-  const double c = q == 0 ? cv : q == 1 ? -sv : q == 2 ? -cv : sv;
-  const double sn = q == 0 ? sv : q == 1 ? cv : q == 2 ? -sv : -cv;
-  return make_float2((float)c, (float)-sn);
-}
-
 // Evenly spaced DM trials, DM_i = DM_0 + i step: the chirp of trial i + 1 is
 // that of trial i times exp(-2 pi i step Q) with Q the per-unit-DM phase of
 // the bin (Eq. 3 is linear in DM), so a tile keeps the chirped spectrum of
@@ -241,9 +216,10 @@ __device__ __forceinline__ float2 expi_neg_turns_fp64(double x) {
 // 512-channel beam, the intensities of 64 trials differ from 64 one-DM calls
 // by 1.1e-7 relative L2).  Entry (b R + r) T + t belongs to thread t alone,
 // as in chirp_phase_per_dm (whose LDS the table takes).
-// rs[] receives exp(-2 pi i DM Q) of this thread's bins for the given DM.
+// rs[] receives (1 + gain) exp(-2 pi i DM Q) of this thread's bins for the
+// given DM.
 template <class S>
-__device__ __forceinline__ void rotation_table(float2* rs, double dm, double fc,
+__device__ __forceinline__ void rotation_table(float2* rs, double dm, float gain, double fc,
                                                const BlockArgs& a, int t) {
   constexpr int N = S::N, R = S::rad_f(S::NP - 1), BPT = N / (R * S::T);
   const double dfn = a.df / (double)N;
@@ -258,7 +234,7 @@ __device__ __forceinline__ void rotation_table(float2* rs, double dm, double fc,
       const double sd = s0 + (double)(r * (N / R) - (2 * r >= R ? N : 0));
       const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                    : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
-      rs[(b * R + r) * S::T + t] = expi_neg_turns_fp64(q - rint(q));
+      rs[(b * R + r) * S::T + t] = expi_neg_turns_fp64(q - rint(q), 1.0 + (double)gain);
     }
   }
 }
@@ -286,10 +262,10 @@ __device__ __forceinline__ void apply_taper(float2* v, int kind, int t) {
   }
 }
 
-// Single DM: multiply by the channel's chirp row h[i] (bins in natural order).
-// The row is read through a buffer resource so that the per-bin offsets are
-// compile-time constants in scalar registers; consecutive lanes read
-// consecutive bins.
+// Single DM: multiply by the channel's chirp row (its layout: see
+// ChirpTableArgs), two bins per 16-byte load.  The row is read through a buffer
+// resource so that the offsets are compile-time constants in scalar
+// registers; consecutive lanes read consecutive entries.
 template <class S>
 __device__ __forceinline__ void chirp_from_table(float2* v, const float2* h, int t) {
   constexpr int N = S::N, R = S::rad_f(S::NP - 1), BPT = N / (R * S::T);
@@ -298,11 +274,12 @@ __device__ __forceinline__ void chirp_from_table(float2* v, const float2* h, int
 #pragma unroll
   for (int b = 0; b < BPT; ++b) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int soff = (S::T * b + r * (N / R)) * 8;
-      const float2 w =
-          __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, t * 8, soff, 0));
-      v[b * R + r] = cmul(v[b * R + r], w);
+    for (int r = 0; r < R; r += 2) {
+      const float4 w = __builtin_bit_cast(
+          float4, __builtin_amdgcn_raw_buffer_load_b128(
+                      rs, t * 16, ((r >> 1) * (N / R) + S::T * b) * 16, 0));
+      v[b * R + r] = cmul(v[b * R + r], make_float2(w.x, w.y));
+      v[b * R + r + 1] = cmul(v[b * R + r + 1], make_float2(w.z, w.w));
     }
   }
 }
@@ -425,7 +402,7 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
   // holds registers (the entries are this thread's own)
   const bool stepped = MULTI && qd != nullptr && a.phase_mode == CDD_PHASE_FP64_REDUCED &&
                        a.dm_step != 0.0;
-  if (stepped) rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], fc, a, t);
+  if (stepped) rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], a.gain, fc, a, t);
   float2 v[S::E];
   load_block<S, DT>(v, a, c, k, t);
   fft_forward<S>(v, lds, a.tw, t);
@@ -443,15 +420,17 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
     // the inverse transform's 1/N (a power of two, so exact) once per item
     constexpr float inv_n = 1.0f / (float)S::N;
     float2 X[S::E];
+    const float gx = stepped ? 0.0f : a.gain;  // (the first rotation carries it)
 #pragma unroll
-    for (int e = 0; e < S::E; ++e) X[e] = make_float2(v[e].x * inv_n, v[e].y * inv_n);
+    for (int e = 0; e < S::E; ++e)
+      X[e] = make_float2(fmaf(v[e].x, gx, v[e].x) * inv_n, fmaf(v[e].y, gx, v[e].y) * inv_n);
     const bool per_dm = qd != nullptr && a.phase_mode == CDD_PHASE_FP64_REDUCED;
     if (stepped) {
       // X becomes the chirped spectrum of the current trial; the table then
       // takes the step rotation
       float2* rs = reinterpret_cast<float2*>(qd);
       step_chirp<S>(X, rs, t);
-      rotation_table<S>(rs, a.dm_step, fc, a, t);
+      rotation_table<S>(rs, a.dm_step, 0.0f, fc, a, t);
       for (int i = 0; i < a.dms.ndm; ++i) {
         int tt = t;
         asm volatile("" : "+v"(tt));
@@ -605,6 +584,8 @@ constexpr int kMixLds =
          cmax(mix_lds_floats<MixSched<4096>>(), mix_lds_floats<MixSched<8192>>()));
 constexpr bool mix_len_ok(int lg) { return lg >= 8 && lg <= 13; }
 static_assert(MixSched<8192>::T == kMixT && MixSched<256>::T <= kMixT, "mixed schedules");
+// (chirp tables are laid out for the default schedules: the same last radix)
+static_assert(MixSched<4096>::rad_f(2) == SchedFor<4096, 0>::type::rad_f(2), "table layout");
 
 template <class S, int DT, bool MULTI>
 __device__ __forceinline__ void mix_unit(const BlockArgs& a, int64_t unit, float* lds) {
@@ -822,11 +803,18 @@ static int resident_workgroups(const void* fn, int threads, int64_t* out) {
   return 0;
 }
 
+// What schedule S needs in the arguments: its twiddles and its gain correction.
+template <class S>
+static int tables_of(BlockArgs& a) {
+  a.gain = gain_of<S>();
+  return twiddles_of<S>(&a.tw);
+}
+
 template <int N, int V>
 static int launch_block_t(const BlockArgs& a0, void* stream) {
   using S = typename SchedFor<N, V>::type;
   BlockArgs a = a0;
-  int err = twiddles_of<S>(&a.tw);
+  int err = tables_of<S>(a);
   if (err) return err;
   const int64_t items = (int64_t)a.nchan * a.nblocks;
   if (items <= 0 || items > 0x7fffffffLL) return (int)hipErrorInvalidValue;
@@ -911,8 +899,47 @@ size_t chirp_table_bytes(const BeamPlan& p) {
   return block_supported(p.N) ? (size_t)p.nchan * p.N * sizeof(float2) : 0;
 }
 
-ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt) {
+// What the one-DM chirp table depends on in schedule V of length N: the radix
+// of the last forward pass (its order) and the gain correction.
+struct TableForm {
+  int radix;
+  float gain;
+};
+template <int N, int V>
+static TableForm table_form() {
+  using S = typename SchedFor<N, V>::type;
+  return {S::rad_f(S::NP - 1), gain_of<S>()};
+}
+static TableForm table_form_of(int N, int v) {
+  switch (N) {
+    case 256: return table_form<256, 0>();
+    case 512: return table_form<512, 0>();
+    case 1024: return table_form<1024, 0>();
+    case 2048: return table_form<2048, 0>();
+    case 4096: return table_form<4096, 0>();  // 16 16 16 in every variant
+    case 8192:
+      switch (v) {
+        case 1: return table_form<8192, 1>();
+        case 2: return table_form<8192, 2>();
+        case 3: return table_form<8192, 3>();
+        case 4: return table_form<8192, 4>();
+        case 5: return table_form<8192, 5>();
+        default: return table_form<8192, 0>();  // 16 16 32
+      }
+    default:
+      switch (v) {
+        case 2: return table_form<16384, 2>();
+        case 3: return table_form<16384, 3>();
+        default: return table_form<16384, 0>();  // 16 32 32
+      }
+  }
+}
+
+ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt, int variant) {
   ChirpTableArgs a{};
+  const TableForm f = table_form_of(p.N, variant);
+  a.lgJ = log2i(p.N / f.radix);
+  a.gain = f.gain;
   a.H = (float2*)H;
   a.f_lo = p.f_lo;
   a.df = p.df;
@@ -927,13 +954,13 @@ ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt) 
   return a;
 }
 
-int launch_chirp_table(const BeamPlan& p, double dm, void* H, void* stream) {
+int launch_chirp_table(const BeamPlan& p, double dm, void* H, void* stream, int variant) {
   if (!block_supported(p.N) || H == nullptr) return (int)hipErrorInvalidValue;
   const int kpt = std::max(1, std::min(8, p.N / 256));
   const int64_t grid = (int64_t)p.nchan * (p.N / (256 * kpt));
   if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL(chirp_table_kernel, dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream,
-                     chirp_table_args(p, dm, H, kpt));
+                     chirp_table_args(p, dm, H, kpt, variant));
   return (int)hipGetLastError();
 }
 
@@ -966,34 +993,34 @@ static int mix_group(int N) {
   return 0;
 }
 
-// Twiddle table of the schedule a launch kind runs for (N, V).
-static int launch_twiddles(int kind, int N, int V, const float2** tw) {
+// tables_of for the schedule a launch kind runs for (N, V).
+static int launch_tables(int kind, int N, int V, BlockArgs& a) {
   if (kind == kLaunchMixed) {
     switch (N) {
-      case 256: return twiddles_of<MixSched<256>>(tw);
-      case 512: return twiddles_of<MixSched<512>>(tw);
-      case 1024: return twiddles_of<MixSched<1024>>(tw);
-      case 2048: return twiddles_of<MixSched<2048>>(tw);
-      case 4096: return twiddles_of<MixSched<4096>>(tw);
-      case 8192: return twiddles_of<MixSched<8192>>(tw);
+      case 256: return tables_of<MixSched<256>>(a);
+      case 512: return tables_of<MixSched<512>>(a);
+      case 1024: return tables_of<MixSched<1024>>(a);
+      case 2048: return tables_of<MixSched<2048>>(a);
+      case 4096: return tables_of<MixSched<4096>>(a);
+      case 8192: return tables_of<MixSched<8192>>(a);
     }
     return (int)hipErrorInvalidValue;
   }
   if (kind == kLaunchBatch && V != 0) {
-    if (N == 4096 && V == 3) return twiddles_of<SchedFor<4096, 3>::type>(tw);
-    if (N == 8192 && V == 1) return twiddles_of<SchedFor<8192, 1>::type>(tw);
-    if (N == 8192 && V == 2) return twiddles_of<SchedFor<8192, 2>::type>(tw);
-    if (N == 16384 && V == 2) return twiddles_of<SchedFor<16384, 2>::type>(tw);
+    if (N == 4096 && V == 3) return tables_of<SchedFor<4096, 3>::type>(a);
+    if (N == 8192 && V == 1) return tables_of<SchedFor<8192, 1>::type>(a);
+    if (N == 8192 && V == 2) return tables_of<SchedFor<8192, 2>::type>(a);
+    if (N == 16384 && V == 2) return tables_of<SchedFor<16384, 2>::type>(a);
     return (int)hipErrorInvalidValue;
   }
   switch (N) {
-    case 256: return twiddles_of<SchedFor<256, 0>::type>(tw);
-    case 512: return twiddles_of<SchedFor<512, 0>::type>(tw);
-    case 1024: return twiddles_of<SchedFor<1024, 0>::type>(tw);
-    case 2048: return twiddles_of<SchedFor<2048, 0>::type>(tw);
-    case 4096: return twiddles_of<SchedFor<4096, 0>::type>(tw);
-    case 8192: return twiddles_of<SchedFor<8192, 0>::type>(tw);
-    case 16384: return twiddles_of<SchedFor<16384, 0>::type>(tw);
+    case 256: return tables_of<SchedFor<256, 0>::type>(a);
+    case 512: return tables_of<SchedFor<512, 0>::type>(a);
+    case 1024: return tables_of<SchedFor<1024, 0>::type>(a);
+    case 2048: return tables_of<SchedFor<2048, 0>::type>(a);
+    case 4096: return tables_of<SchedFor<4096, 0>::type>(a);
+    case 8192: return tables_of<SchedFor<8192, 0>::type>(a);
+    case 16384: return tables_of<SchedFor<16384, 0>::type>(a);
   }
   return (int)hipErrorInvalidValue;
 }
@@ -1037,7 +1064,7 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
     const BeamPlan& p = *beams[b].p;
     ht[i] = make_args(p, beams[b].co, beams[b].xt, beams[b].dms, beams[b].P, nullptr,
                       (const float2*)(H ? H[b] : nullptr));
-    int err = launch_twiddles(kind, p.N, out.variant, &ht[i].tw);
+    int err = launch_tables(kind, p.N, out.variant, ht[i]);
     if (err) return err;
     ht[i].item0 = total;
     const int64_t items = (int64_t)p.nchan * beams[b].co.nblocks;

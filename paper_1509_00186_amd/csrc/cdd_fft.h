@@ -212,6 +212,46 @@ struct DftTw {
   }
 };
 
+// DFT of R = 4 Q points whose input r takes w^r, from the factored twiddles
+// h[n1 - 1] = w^(Q n1), n1 = 1 .. 3, and l[n2 - 1] = w^n2, n2 = 1 .. Q - 1
+// (r = Q n1 + n2): the first radix-4 stage takes h, the same three factors in
+// each of its Q groups, and the second stage takes l[n2 - 1] W_R^(n2 k1).  Q + 2
+// twiddles instead of R - 1, for 1.3 operations per point more (R = 16) --
+// the loads were what bounded the passes (see PassTw).
+template <int R, int DIR>
+struct DftTwFac {
+  static __device__ __forceinline__ void run(float2* v, const float2* h, const float2* l) {
+    constexpr int Q = R / 4;
+    float2 y[R];
+#pragma unroll
+    for (int n2 = 0; n2 < Q; ++n2) {
+      const float2 a = v[n2];
+      const float2 b = cmul(v[Q + n2], h[0]);
+      const float2 t0 = cfma(v[2 * Q + n2], h[1], a);
+      const float2 t1 = ctwice_minus(a, t0);
+      const float2 t2 = cfma(v[3 * Q + n2], h[2], b);
+      const float2 t3 = mul_i<DIR>(ctwice_minus(b, t2));
+      y[n2 * 4 + 0] = cadd(t0, t2);
+      y[n2 * 4 + 1] = cadd(t1, t3);
+      y[n2 * 4 + 2] = csub(t0, t2);
+      y[n2 * 4 + 3] = csub(t1, t3);
+    }
+    sfor<0, 4>([&](auto K1) {
+      constexpr int k1 = decltype(K1)::value;
+      float2 s[Q], u[Q > 1 ? Q - 1 : 1];
+      s[0] = y[k1];
+      sfor<1, Q>([&](auto N2) {
+        constexpr int n2 = decltype(N2)::value;
+        s[n2] = y[n2 * 4 + k1];
+        u[n2 - 1] = twc<R, n2 * k1, DIR>(l[n2 - 1]);
+      });
+      if constexpr (Q > 1) DftTw<Q, DIR>::run(s, u);
+#pragma unroll
+      for (int k2 = 0; k2 < Q; ++k2) v[k1 + 4 * k2] = s[k2];
+    });
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Schedules: threads per workgroup and forward radix order per length
 // ---------------------------------------------------------------------------
@@ -233,6 +273,12 @@ constexpr int xpad_shift(int R, int Ns) {
 template <int TS>
 __device__ __forceinline__ constexpr int xpad(int i) { return i + ((i >> 5) << TS); }
 
+// Twiddle table of a pass: its entries and their places (see PassTw).
+constexpr int tw_count(int R) { return R == 2 ? 1 : R / 4 + 2; }  // twiddles per butterfly
+constexpr int tw_power(int R, int i) { return R == 2 ? 1 : i < 3 ? (i + 1) * (R / 4) : i - 2; }
+constexpr int tw_index(int i, int k, int NS) { return 2 * ((i >> 1) * NS + k) + (i & 1); }
+constexpr int tw_entries(int R, int NS) { return (tw_count(R) + 1) / 2 * 2 * NS; }
+
 template <int N_, int T_, int A, int B, int C, int D, bool SPLIT_ = true, bool PF_ = false,
           int MINB_ = 1>
 struct Sched {
@@ -253,15 +299,15 @@ struct Sched {
     for (int i = 0; i < q; ++i) s *= rad_i(i);
     return s;
   }
-  // twiddle tables (R x NS entries) for every pass after the first
+  // twiddle tables of every pass after the first
   static constexpr int tw_f(int p) {
     int o = 0;
-    for (int i = 1; i < p; ++i) o += ns_f(i) * rad_f(i);
+    for (int i = 1; i < p; ++i) o += tw_entries(rad_f(i), ns_f(i));
     return o;
   }
   static constexpr int tw_i(int q) {
     int o = tw_f(NP);
-    for (int i = 1; i < q; ++i) o += ns_i(i) * rad_i(i);
+    for (int i = 1; i < q; ++i) o += tw_entries(rad_i(i), ns_i(i));
     return o;
   }
   static constexpr int tw_total() { return tw_i(NP); }
@@ -287,28 +333,37 @@ __device__ __forceinline__ int lpad(int i) { return i + (i >> 4); }
 // Stockham pass pieces
 // ---------------------------------------------------------------------------
 // Twiddles of one pass (radix R, span NS) for this thread's butterflies,
-// loaded ahead of the exchange that precedes the pass.  The table holds
-// W^(r k) at r * NS + k, so the lanes of a wave, whose k are consecutive,
-// read consecutive entries.  The loads go through a buffer resource on the
-// pass's table (scalar base, constant offset r NS per load), so each needs
-// only the thread's offset k, formed once per butterfly group, and no
-// 64-bit address arithmetic.
+// loaded ahead of the exchange that precedes the pass: the factored form of
+// DftTwFac, entries w^Q, w^(2Q), w^(3Q), w, ..., w^(Q-1) with w = W^k, Q = R/4
+// (radix 2: w alone).  Two entries lie side by side (tw_index), so one 16-byte
+// load gives a lane two of them and the lanes of a wave, whose k are
+// consecutive, read consecutive addresses: three loads for radix 16 instead of
+// 15 of 8 bytes.  A wave's load of 8 or of 16 bytes per lane alike occupies the
+// return path of the L1 for 16 clocks, and with a load per twiddle that path
+// was busy for 84-92% of the block kernels' time and bounded them.  The loads go
+// through a buffer resource on the pass's table (scalar base, constant offset
+// per load), so each needs only the thread's offset k, formed once per
+// butterfly group, and no 64-bit address arithmetic.
+
 template <class S, int R, int NS, int TWOFF>
 struct PassTw {
   static constexpr int BPT = S::N / (R * S::T);
-  static constexpr int CNT = NS > 1 ? BPT * (R - 1) : 1;
-  float2 w[CNT];
+  static constexpr int PER = (tw_count(R) + 1) & ~1;  // per butterfly, with padding
+  float2 w[NS > 1 ? BPT * PER : 1];
   __device__ __forceinline__ void load(const float2* __restrict__ tw, int t) {
     if constexpr (NS > 1) {
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)(tw + TWOFF), (short)0, R * NS * 8, 0x00020000);
+          (void*)(tw + TWOFF), (short)0, tw_entries(R, NS) * 8, 0x00020000);
 #pragma unroll
       for (int b = 0; b < BPT; ++b) {
         const int k = (t + S::T * b) & (NS - 1);
 #pragma unroll
-        for (int r = 1; r < R; ++r)
-          w[b * (R - 1) + r - 1] = __builtin_bit_cast(
-              float2, __builtin_amdgcn_raw_buffer_load_b64(rs, k * 8, r * NS * 8, 0));
+        for (int i = 0; i < PER; i += 2) {
+          const float4 q = __builtin_bit_cast(
+              float4, __builtin_amdgcn_raw_buffer_load_b128(rs, k * 16, i * NS * 8, 0));
+          w[b * PER + i] = make_float2(q.x, q.y);
+          w[b * PER + i + 1] = make_float2(q.z, q.w);
+        }
       }
     }
   }
@@ -322,8 +377,10 @@ __device__ __forceinline__ void butterflies(float2* v, const PassTw<S, R, NS, TW
 #pragma unroll
   for (int b = 0; b < BPT; ++b) {
     float2* w = v + b * R;
-    if constexpr (NS > 1)
-      DftTw<R, DIR>::run(w, pt.w + b * (R - 1));
+    if constexpr (NS > 1 && R == 2)
+      DftTw<2, DIR>::run(w, pt.w + b * pt.PER);
+    else if constexpr (NS > 1)
+      DftTwFac<R, DIR>::run(w, pt.w + b * pt.PER, pt.w + b * pt.PER + 3);
     else
       Dft<R, DIR>::run(w);
   }
@@ -437,8 +494,58 @@ __device__ __forceinline__ float taper_gain(int kind, float x) {
   return 1.0f;
 }
 
-// Chirp table of one DM: H[c*N + i] = exp(-2 pi i q)/N for bin i of channel c
-// (signed bin s = i or i - N, offset f = s*df/N from the channel centre fc),
+// scale exp(-2 pi i x) for |x| <= 1/2 turn, rounded to FP32: the quadrant
+// n = rint(4x) is taken out exactly, and the sine and cosine of the remaining
+// angle (at most pi/4) come from their Taylor series in FP64 through the
+// 11th and 12th powers (truncation below 1e-11, far under FP32 rounding).
+__device__ __forceinline__ float2 expi_neg_turns_fp64(double x, double scale) {
+  const double n = rint(4.0 * x);
+  const double th = 6.283185307179586 * fma(n, -0.25, x);
+  const double t2 = th * th;
+  double sp = fma(t2, -2.505210838544172e-08, 2.755731922398589e-06);  // 1/11!, 1/9!
+  sp = fma(t2, sp, -1.984126984126984e-04);                            // 1/7!
+  sp = fma(t2, sp, 8.333333333333333e-03);                             // 1/5!
+  sp = fma(t2, sp, -1.666666666666667e-01);                            // 1/3!
+  const double sv = fma(th * t2, sp, th);
+  double cp = fma(t2, 2.087675698786810e-09, -2.755731922398589e-07);  // 1/12!, 1/10!
+  cp = fma(t2, cp, 2.480158730158730e-05);                             // 1/8!
+  cp = fma(t2, cp, -1.388888888888889e-03);                            // 1/6!
+  cp = fma(t2, cp, 4.166666666666667e-02);                             // 1/4!
+  cp = fma(t2, cp, -0.5);
+  const double cv = fma(t2, cp, 1.0);
+  // rotate by the quadrant: exp(2 pi i x) = i^n exp(i th)
+  const int q = ((int)n) & 3;
+  const double c = q == 0 ? cv : q == 1 ? -sv : q == 2 ? -cv : sv;
+  const double sn = q == 0 ? sv : q == 1 ? cv : q == 2 ? -sv : -cv;
+  return make_float2((float)(scale * c), (float)(-scale * sn));
+}
+
+// exp(-2 pi i x) for |x| <= 1/2 turn to within an FP32 rounding or two: the
+// quadrant n = rint(4x) taken out exactly in FP64, then the Taylor series of
+// sine and cosine on [-pi/4, pi/4] in FP32 through the 9th and 10th powers
+// (truncation below 2e-9).  About 20 FP32 operations; the hardware sine and
+// cosine have an absolute error of 1.2e-7, more than the transforms around them.
+__device__ __forceinline__ float2 expi_neg_turns_fp32(double x) {
+  const double n = rint(4.0 * x);
+  const float d = (float)fma(n, -0.25, x);
+  const float th = fmaf(d, 6.2831855f, d * -1.7484556e-07f);  // 2 pi in two parts
+  const float t2 = th * th;
+  float sp = fmaf(t2, 2.7557319e-06f, -1.9841270e-04f);
+  sp = fmaf(t2, sp, 8.3333333e-03f);
+  sp = fmaf(t2, sp, -1.6666667e-01f);
+  const float sv = fmaf(th * t2, sp, th);
+  float cp = fmaf(t2, -2.7557319e-07f, 2.4801587e-05f);
+  cp = fmaf(t2, cp, -1.3888889e-03f);
+  cp = fmaf(t2, cp, 4.1666667e-02f);
+  cp = fmaf(t2, cp, -0.5f);
+  const float cv = fmaf(t2, cp, 1.0f);
+  const int q = (int)n & 3;  // exp(2 pi i x) = i^q exp(i th)
+  const float c = q & 1 ? sv : cv, sn = q & 1 ? cv : sv;
+  return make_float2((q == 1 || q == 2) ? -c : c, q >= 2 ? sn : -sn);
+}
+
+// Chirp table of one DM: exp(-2 pi i q)/N for every bin i of channel c, in row
+// H + c*N (signed bin s = i or i - N, offset f = s*df/N from the channel centre fc),
 // q = D*DM*f^2/(fc^2 (fc + f)) turns (Eq. 3), evaluated in FP64 exactly as
 // apply_chirp does -- q = B s^2 / (1 + beta s) with B = D*DM*(df/N)^2/fc^3 and
 // beta = (df/N)/fc, the division replaced by the series s^2 (B - B beta s +
@@ -448,12 +555,22 @@ __device__ __forceinline__ float taper_gain(int kind, float x) {
 // reduction r = q - rint(q) to [-1/2, 1/2] turns is FP64; sin/cos of 2 pi r
 // are FP32.  The FP32 phase mode forms q itself in FP32 (precision study).
 // The taper (Sec. 2.2) scales the entry with the 1/N of the inverse transform.
+// Order of a row: the block kernel's threads hold bins j + r N/R (R the radix
+// of its last forward pass, r < R); the bins of even r and of r + 1 lie side by
+// side at 2 (r/2 N/R + j), so that one 16-byte load gives a lane two of them.
 struct ChirpTableArgs {
   float2* H;
   double f_lo, df, dconst, dm;
-  int32_t lgN, kpt, phase_mode, taper, exact_div;
+  int32_t lgN, lgJ, kpt, phase_mode, taper, exact_div;  // lgJ = log2(N/R)
+  float gain;    // relative correction of the transforms' gain (gain_of)
   uint32_t nwg;  // workgroups of 256 threads covering the table (nchan N / (256 kpt))
 };
+
+// The bin at position e of a row.
+__device__ __forceinline__ int chirp_bin(int e, int lgJ) {
+  const int q = e >> 1;
+  return (q & ((1 << lgJ) - 1)) + ((2 * (q >> lgJ) + (e & 1)) << lgJ);
+}
 
 // Entries of table workgroup wg (< a.nwg), thread tid: kpt entries of one
 // channel, 256 apart.
@@ -475,37 +592,36 @@ __device__ __forceinline__ void chirp_table_part(const ChirpTableArgs& a, unsign
     const double beta = dfn / fc;
     const double Bb = B * beta, Bbb = Bb * beta;
     for (int k = 0; k < kpt; ++k) {
-      const int i = i0 + 256 * k;
+      const int e = i0 + 256 * k, i = chirp_bin(e, a.lgJ);
       const int s = i < N / 2 ? i : i - N;
       const double sd = (double)s;
       const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                  : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
-      // r in [-1/2, 1/2] turns: the hardware sine and cosine take turns
-      // (absolute error about 1.2e-7)
-      const float r = (float)(q - rint(q));
+      const float2 h = expi_neg_turns_fp32(q - rint(q));
       const float gn = taper_gain<false>(taper, (float)s * inv_n) * inv_n;
-      row[i] = make_float2(__builtin_amdgcn_cosf(r) * gn, -__builtin_amdgcn_sinf(r) * gn);
+      row[e] = make_float2(fmaf(h.x, a.gain, h.x) * gn, fmaf(h.y, a.gain, h.y) * gn);
     }
   } else {
     const float fcf = (float)fc;
     const float Af = (float)(dconst * dm) / (fcf * fcf);
     const float dff = (float)df * inv_n;
     for (int k = 0; k < kpt; ++k) {
-      const int i = i0 + 256 * k;
+      const int e = i0 + 256 * k, i = chirp_bin(e, a.lgJ);
       const int s = i < N / 2 ? i : i - N;
       const float f = (float)s * dff;
       const float q = Af * (f * f) / (fcf + f);
       float sn, cs;
       sincospif(2.0f * q, &sn, &cs);
       const float gn = taper_gain<false>(taper, (float)s * inv_n) * inv_n;
-      row[i] = make_float2(cs * gn, -sn * gn);
+      row[e] = make_float2(fmaf(cs, a.gain, cs) * gn, -fmaf(sn, a.gain, sn) * gn);
     }
   }
 }
 
-// Host: the table arguments of beam p at one DM (cdd_block.hip).
+// Host: the table arguments of beam p at one DM, for the schedule `variant` of
+// its length (cdd_block.hip).
 struct BeamPlan;
-ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt);
+ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt, int variant);
 
 // cos and sin of 2 pi k / 64 for the 64 octant-of-an-octant rotations.
 struct RotTable {
@@ -543,29 +659,87 @@ __device__ __forceinline__ float2 expi_neg_turns(double r) {
   return expi_neg_turns64(q * 64.0);
 }
 
-// Host: FP64 twiddle tables of a schedule, R x NS entries per pass after the
-// first (entry r * NS + k = W^(r k)); forward tables then inverse
-// (conjugate) tables.
+// Host: FP64 twiddle tables of a schedule for every pass after the first
+// (entry i of butterfly k = W^(tw_power(R, i) k) at tw_index(i, k, NS)); forward
+// tables then inverse (conjugate) tables.
+inline void make_pass_twiddles(float2* tw, int R, int ns, int sign) {
+  for (int k = 0; k < ns; ++k)
+    for (int i = 0; i < tw_count(R); ++i) {
+      const double ang = sign * 2.0 * M_PI * (double)(tw_power(R, i) * k) / (double)(ns * R);
+      tw[tw_index(i, k, ns)] = make_float2((float)std::cos(ang), (float)std::sin(ang));
+    }
+}
 template <class S>
 std::vector<float2> make_twiddles() {
   std::vector<float2> tw(S::tw_total() > 0 ? S::tw_total() : 1);
-  for (int p = 1; p < S::NP; ++p) {
-    const int R = S::rad_f(p), ns = S::ns_f(p), off = S::tw_f(p);
-    for (int k = 0; k < ns; ++k)
-      for (int r = 0; r < R; ++r) {
-        const double ang = -2.0 * M_PI * (double)(r * k) / (double)(ns * R);
-        tw[off + r * ns + k] = make_float2((float)std::cos(ang), (float)std::sin(ang));
-      }
-  }
-  for (int q = 1; q < S::NP; ++q) {
-    const int R = S::rad_i(q), ns = S::ns_i(q), off = S::tw_i(q);
-    for (int k = 0; k < ns; ++k)
-      for (int r = 0; r < R; ++r) {
-        const double ang = 2.0 * M_PI * (double)(r * k) / (double)(ns * R);
-        tw[off + r * ns + k] = make_float2((float)std::cos(ang), (float)std::sin(ang));
-      }
-  }
+  for (int p = 1; p < S::NP; ++p)
+    make_pass_twiddles(tw.data() + S::tw_f(p), S::rad_f(p), S::ns_f(p), -1);
+  for (int q = 1; q < S::NP; ++q)
+    make_pass_twiddles(tw.data() + S::tw_i(q), S::rad_i(q), S::ns_i(q), +1);
   return tw;
+}
+
+// Mean gain of a schedule's passes.  The FP32 rounding of a rotation (c, s)
+// leaves c^2 + s^2 a little off 1, and the few constants inside the butterflies
+// all fall short of it (cos and sin of pi/8 by 2.9e-8, of pi/4 by 1.7e-8), so
+// every pass loses about 1e-8 of the amplitude, the same for all data: it was
+// the largest error of summed intensities, in which random rounding averages
+// out (512 channels: 2.5e-7 relative, 7e-8 without it).  The chirp takes the
+// loss out again, as a relative correction applied before its entries are
+// rounded.
+// Power gain of the constants of an in-register DFT of R points:
+inline double dft_const_gain(int R) {
+  if (R <= 4) return 1.0;
+  const int Q = R / 4;
+  double sum = 0;
+  for (int n2 = 0; n2 < Q; ++n2)
+    for (int k1 = 0; k1 < 4; ++k1) {
+      const double ang = 2.0 * M_PI * (double)(n2 * k1) / R;
+      const double c = (float)std::cos(ang), s = (float)std::sin(ang);
+      sum += (4 * n2 * k1) % R == 0 ? 1.0 : c * c + s * s;
+    }
+  return sum / R * dft_const_gain(Q);
+}
+// ... and of one pass's twiddles (tw as make_pass_twiddles fills it).
+inline double pass_tw_gain(const float2* tw, int R, int ns) {
+  double sum = 0;
+  for (int k = 0; k < ns; ++k) {
+    auto g = [&](int i) {
+      const float2 w = tw[tw_index(i, k, ns)];
+      return (double)w.x * w.x + (double)w.y * w.y;
+    };
+    if (R == 2) {
+      sum += 0.5 * (1.0 + g(0));
+      continue;
+    }
+    const int Q = R / 4;
+    double h = 1.0, l = 1.0;
+    for (int i = 0; i < 3; ++i) h += g(i);
+    for (int i = 0; i < Q - 1; ++i) l += g(3 + i);
+    sum += h / 4 * l / Q;
+  }
+  return sum / ns;
+}
+// Relative correction of the amplitude after the forward and the inverse
+// transform of schedule S (exact: the first pass has no rounded constants).
+template <class S>
+double gain_correction(bool exact_first = false) {
+  const std::vector<float2> tw = make_twiddles<S>();
+  double lg = 0;
+  for (int p = 0; p < S::NP; ++p) {
+    if (p > 0) {
+      lg += std::log(pass_tw_gain(tw.data() + S::tw_f(p), S::rad_f(p), S::ns_f(p)));
+      lg += std::log(pass_tw_gain(tw.data() + S::tw_i(p), S::rad_i(p), S::ns_i(p)));
+    }
+    if (p > 0 || !exact_first) lg += std::log(dft_const_gain(S::rad_f(p)));
+    lg += std::log(dft_const_gain(S::rad_i(p)));
+  }
+  return -0.5 * lg;
+}
+template <class S>
+float gain_of() {
+  static const float g = (float)gain_correction<S>();
+  return g;
 }
 
 // Device copy of a host-built table, created once per (device, key) and kept

@@ -91,7 +91,7 @@ static int run_single(Aux& ax, const BeamPlan& p, const void* voltages, double d
     if ((e = hipEventRecord(e0, S)) != hipSuccess) return (int)e;
     if ((e = hipStreamWaitEvent(A, e0, 0)) != hipSuccess) return (int)e;
     if ((err = stage_begin(kStageDelays, A, &tok))) return err;
-    if (H && (err = launch_chirp_table(p, dm, H, A))) return err;
+    if (H && (err = launch_chirp_table(p, dm, H, A, p.variant))) return err;
     if ((err = launch_delays(p, tile, d, A))) return err;
     if ((err = stage_end(kStageDelays, A, tok))) return err;
     eA = take(ax);
@@ -103,7 +103,7 @@ static int run_single(Aux& ax, const BeamPlan& p, const void* voltages, double d
   for (int pol = 0; pol < npol; ++pol) {
     if ((err = stage_begin(kStageTranspose, S, &tok))) return err;
     if (pol == 0 && fused)
-      err = launch_transpose_chirp(p, voltages, xt, dm, H, S, d);
+      err = launch_transpose_chirp(p, voltages, xt, dm, H, S, d, p.variant);
     else
       err = launch_transpose((const char*)voltages + pol * rec, xt, p.dtype, p.nsamp, p.nchan,
                              xt_stride(p), S);
@@ -221,7 +221,7 @@ int run_pipelined(const BeamPlan& p, const void* voltages, double dm, char* xt, 
   void* tok = nullptr;
   if ((err = stage_begin(kStageDelays, S, &tok))) return err;
   if ((err = launch_delays(p, tile, d, S))) return err;
-  if ((err = launch_chirp_table(p, dm, H, S))) return err;
+  if ((err = launch_chirp_table(p, dm, H, S, p.variant))) return err;
   if ((err = stage_end(kStageDelays, S, tok))) return err;
   std::vector<hipEvent_t> evT(C), evB(C);
   for (int i = 0; i < C; ++i) {
