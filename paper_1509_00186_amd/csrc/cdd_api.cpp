@@ -325,25 +325,33 @@ extern "C" cdd_status cdd_incoherent(const void* voltages, int32_t dtype, int64_
                   workspace ? ws_bytes : (size_t)0);
     if (!aligned256(workspace)) return fail(CDD_EINVAL, "workspace must be 256-byte aligned");
     char* ws = (char*)workspace;
-    const void* xt = voltages;
     int e = 0;
-    if (p.nchan > 1) {
-      if ((e = launch_transposed(p, voltages, ws + lay.xt_off, stream)))
-        return device_fail("transpose launch", e);
-      xt = ws + lay.xt_off;
-    }
     float* P = chan_intensity ? chan_intensity : (float*)(ws + lay.p_off);
     int32_t* d = (int32_t*)(ws + lay.d_off);
-    DmTile tile;
-    tile.ndm = 1;
-    tile.dm[0] = dm;
     void* tok = nullptr;
-    if ((e = stage_begin(kStageDelays, stream, &tok)) || (e = launch_delays(p, tile, d, stream)) ||
-        (e = stage_end(kStageDelays, stream, tok)))
-      return device_fail("delay launch", e);
-    if ((e = stage_begin(kStageBlock, stream, &tok)) || (e = launch_detect(p, xt, P, stream)) ||
-        (e = stage_end(kStageBlock, stream, tok)))
-      return device_fail("detect launch", e);
+    if (detect_tiled_fits(p)) {
+      // detection straight from the time-major record, with the delays
+      if ((e = stage_begin(kStageBlock, stream, &tok)) ||
+          (e = launch_detect_tiled(p, voltages, P, dm, d, stream)) ||
+          (e = stage_end(kStageBlock, stream, tok)))
+        return device_fail("detect launch", e);
+    } else {
+      const void* xt = voltages;
+      if (p.nchan > 1) {
+        if ((e = launch_transposed(p, voltages, ws + lay.xt_off, stream)))
+          return device_fail("transpose launch", e);
+        xt = ws + lay.xt_off;
+      }
+      DmTile tile;
+      tile.ndm = 1;
+      tile.dm[0] = dm;
+      if ((e = stage_begin(kStageDelays, stream, &tok)) ||
+          (e = launch_delays(p, tile, d, stream)) || (e = stage_end(kStageDelays, stream, tok)))
+        return device_fail("delay launch", e);
+      if ((e = stage_begin(kStageBlock, stream, &tok)) ||
+          (e = launch_detect(p, xt, P, stream)) || (e = stage_end(kStageBlock, stream, tok)))
+        return device_fail("detect launch", e);
+    }
     if ((e = stage_begin(kStageDsum, stream, &tok)) ||
         (e = launch_dsum(p, 1, P, d, intensity, coverage, p.t_int, stream)) ||
         (e = stage_end(kStageDsum, stream, tok)))

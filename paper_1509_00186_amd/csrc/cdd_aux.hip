@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "cdd_fft.h"
 #include "cdd_internal.h"
@@ -28,6 +29,21 @@ struct DelayArgs {
   double dm, f_centre, bw, df, dconst;
   int32_t nchan, n_int;
 };
+
+static DelayArgs delay_args(const BeamPlan& p, double dm, int32_t* delays) {
+  DelayArgs dl{};
+  if (delays) {
+    dl.d = delays;
+    dl.dm = dm;
+    dl.f_centre = p.f_centre;
+    dl.bw = p.bw;
+    dl.df = p.df;
+    dl.dconst = p.dconst;
+    dl.nchan = p.nchan;
+    dl.n_int = p.n_int;
+  }
+  return dl;
+}
 
 // ---------------------------------------------------------------------------
 // Time-major [nsamp][nchan] -> channel-major [nchan][nsamp].
@@ -170,17 +186,7 @@ int launch_transpose_chirp(const BeamPlan& p, const void* in, void* out, double 
   int kpt = 1;
   while ((int64_t)p.nchan * (p.N / (256 * kpt)) > n && 256 * kpt * 2 <= p.N) kpt *= 2;
   const ChirpTableArgs ct = chirp_table_args(p, dm, H, kpt, variant);
-  DelayArgs dl{};
-  if (delays) {
-    dl.d = delays;
-    dl.dm = dm;
-    dl.f_centre = p.f_centre;
-    dl.bw = p.bw;
-    dl.df = p.df;
-    dl.dconst = p.dconst;
-    dl.nchan = p.nchan;
-    dl.n_int = p.n_int;
-  }
+  const DelayArgs dl = delay_args(p, dm, delays);
   hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)n), dim3(256), 0, (hipStream_t)stream,
                      (const unsigned short*)in, (unsigned short*)out, p.nsamp, p.nchan,
                      (int32_t)tiles_c, (int32_t)(((uintptr_t)in & 7u) == 0), xt_stride(p), ct,
@@ -271,6 +277,121 @@ int launch_detect(const BeamPlan& p, const void* xt, float* P, void* stream) {
   else
     hipLaunchKernelGGL(detect_kernel<CDD_CF32>, grid, dim3(256), 0, (hipStream_t)stream, xt, P,
                        xt_stride(p), p.t_int, p.n_int);
+  return (int)hipGetLastError();
+}
+
+// The same straight from the time-major record, without a channel-major copy:
+// a workgroup takes 32 outputs of a run of CH = 32 CPT (or 64) channels, each
+// lane the n_int samples of CPT adjacent channels, and turns the sums through
+// LDS so that both sides are whole runs (CH samples in, 32 floats out).  It is
+// bound by HBM: the record is read once and P written once, where the copy
+// read and wrote the record again (512 channels x 250,000 int8 samples, n_int
+// 4: 92 + 118 us for copy and detection, 76 us here).  NI: n_int at compile
+// time (0: any).  The last workgroup also writes the channel delays.
+// A long integration leaves few outputs, so few workgroups: from
+// kDetectTiledMax samples on the copy and detect_kernel are taken instead.
+constexpr int kDetectTiledMax = 64;
+
+template <int DT, int CPT, int NI>
+__global__ __launch_bounds__(256) void detect_tiled_kernel(const void* __restrict__ in,
+                                                           float* __restrict__ P, int32_t nchan,
+                                                           int32_t tiles_c, int64_t t_int,
+                                                           int32_t n_int_, const DelayArgs dl) {
+  constexpr int LC = CPT == 1 ? 64 : 32;   // lanes along channels
+  constexpr int CH = LC * CPT;             // channels per workgroup
+  constexpr int UP = 256 / LC, U = 32;     // outputs per step and per workgroup
+  __shared__ float tile[U][CH + 1];
+  const int n_int = NI ? NI : n_int_;
+  const int c0 = (int)(blockIdx.x % tiles_c) * CH;
+  const int64_t u0 = (int64_t)(blockIdx.x / tiles_c) * U;
+  const int cl = ((int)threadIdx.x % LC) * CPT, ul = threadIdx.x / LC;
+  const bool in_c = c0 + cl < nchan;  // (CPT divides nchan)
+#pragma unroll
+  for (int i = 0; i < U / UP; ++i) {
+    const int64_t u = u0 + ul + i * UP;
+    float acc[CPT];
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) acc[q] = 0.f;
+    if (in_c && u < t_int) {
+      const int64_t at = u * n_int * nchan + c0 + cl;
+      auto add = [&](int r) {
+        if constexpr (DT == CDD_CF32) {
+          const float2 z = ((const float2*)in)[at + (int64_t)r * nchan];
+          acc[0] += z.x * z.x + z.y * z.y;
+        } else {
+          unsigned w[(CPT + 1) / 2];
+          if constexpr (CPT == 4) {
+            const uint2 x = *(const uint2*)((const unsigned short*)in + at + (int64_t)r * nchan);
+            w[0] = x.x;
+            w[1] = x.y;
+          } else {
+            w[0] = ((const unsigned short*)in)[at + (int64_t)r * nchan];
+          }
+#pragma unroll
+          for (int q = 0; q < CPT; ++q) {
+            const unsigned h = w[q / 2] >> (16 * (q & 1));
+            const float re = (float)(signed char)(h & 0xff);
+            const float im = (float)(signed char)((h >> 8) & 0xff);
+            acc[q] += re * re + im * im;
+          }
+        }
+      };
+      if constexpr (NI > 0) {
+#pragma unroll
+        for (int r = 0; r < NI; ++r) add(r);
+      } else {
+#pragma unroll 4
+        for (int r = 0; r < n_int; ++r) add(r);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) tile[ul + i * UP][cl + q] = acc[q];
+  }
+  __syncthreads();
+  // 32 lanes per channel row
+  const int us = threadIdx.x & 31;
+  for (int c = threadIdx.x >> 5; c < CH && c0 + c < nchan; c += 8)
+    if (u0 + us < t_int) P[(int64_t)(c0 + c) * t_int + u0 + us] = tile[us][c];
+  if (dl.d != nullptr && blockIdx.x == gridDim.x - 1)
+    for (int c = threadIdx.x; c < dl.nchan; c += 256)
+      dl.d[c] = channel_delay(c, dl.dm, dl.nchan, dl.f_centre, dl.bw, dl.df, dl.dconst, dl.n_int);
+}
+
+bool detect_tiled_fits(const BeamPlan& p) {
+  if (p.nchan < 2 || p.n_int > kDetectTiledMax) return false;
+  return ((int64_t)(p.nchan + 63) / 64) * ((p.t_int + 31) / 32) <= 0x7fffffffLL;
+}
+
+template <int DT, int CPT>
+static void detect_tiled_launch(const BeamPlan& p, const void* in, float* P, const DelayArgs& dl,
+                                hipStream_t st) {
+  constexpr int CH = CPT == 1 ? 64 : 32 * CPT;
+  const int32_t tc = (p.nchan + CH - 1) / CH;
+  const dim3 grid((unsigned)(tc * ((p.t_int + 31) / 32))), block(256);
+  auto go = [&](auto NI) {
+    hipLaunchKernelGGL((detect_tiled_kernel<DT, CPT, decltype(NI)::value>), grid, block, 0, st,
+                       in, P, p.nchan, tc, p.t_int, p.n_int, dl);
+  };
+  switch (p.n_int) {
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    case 8: return go(std::integral_constant<int, 8>{});
+    default: return go(std::integral_constant<int, 0>{});
+  }
+}
+
+int launch_detect_tiled(const BeamPlan& p, const void* in, float* P, double dm, int32_t* delays,
+                        void* stream) {
+  if (!detect_tiled_fits(p)) return (int)hipErrorInvalidValue;
+  const DelayArgs dl = delay_args(p, dm, delays);
+  hipStream_t st = (hipStream_t)stream;
+  if (p.dtype == CDD_CF32)
+    detect_tiled_launch<CDD_CF32, 1>(p, in, P, dl, st);
+  else if (p.nchan % 4 == 0 && ((uintptr_t)in & 7u) == 0)
+    detect_tiled_launch<CDD_CI8, 4>(p, in, P, dl, st);  // rows of whole 8-byte words
+  else
+    detect_tiled_launch<CDD_CI8, 1>(p, in, P, dl, st);
   return (int)hipGetLastError();
 }
 

@@ -186,6 +186,10 @@ cdd_status run_tile(const BeamPlan& p, const void* voltages, const DmTile& tile,
 cdd_status device_fail(const char* what, int err);
 // P[c][u] = sum of |x[c][u n_int + r]|^2, r < n_int (channel-major x).
 int launch_detect(const BeamPlan& p, const void* xt, float* P, void* stream);
+// The same from the time-major record, where it fits; also the channel delays.
+bool detect_tiled_fits(const BeamPlan& p);
+int launch_detect_tiled(const BeamPlan& p, const void* in, float* P, double dm, int32_t* delays,
+                        void* stream);
 int launch_fold(const float* I, int64_t t_int, double period, double phase0, int32_t nbins,
                 float* profile, int32_t* counts, void* stream);
 int launch_dsum(const BeamPlan& p, int ndm, const float* P, const int32_t* d,
