@@ -231,7 +231,7 @@ cdd_status cdd_incoherent(const void* voltages, int32_t dtype, int64_t nsamp,
  * (the folded profiles the paper compares in Sec. 4.5).  Sample u goes to bin
  * floor(frac(u / period + phase0) * nbins) (clamped to nbins - 1),
  * frac(x) = x - floor(x), all in FP64; profile[b] is the sum of its samples
- * in ascending u (accumulated in FP64, stored as FP32) and counts[b] their
+ * (accumulated in FP64 in a fixed order, stored as FP32) and counts[b] their
  * number.
  *   intensity  device float [t_int] (e.g. the output of cdd_dedisperse)
  *   period     in samples of the series, > 1; phase0 in turns, finite
