@@ -623,42 +623,6 @@ __device__ __forceinline__ void chirp_table_part(const ChirpTableArgs& a, unsign
 struct BeamPlan;
 ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt, int variant);
 
-// cos and sin of 2 pi k / 64 for the 64 octant-of-an-octant rotations.
-struct RotTable {
-  float cs[64][2];  // cos, sin of 2 pi k / 64
-};
-constexpr RotTable make_rot() {
-  RotTable t{};
-  for (int i = 0; i < 64; ++i) {
-    t.cs[i][0] = (float)ct_cos2pi(i, 64);
-    t.cs[i][1] = (float)ct_sin2pi(i, 64);
-  }
-  return t;
-}
-static __constant__ RotTable kRot = make_rot();
-
-// exp(-2 pi i r) for r given as r64 = 64 r turns in FP64 (any magnitude
-// below 2^31): r64 = k + d with k integer and |d| <= 1/2; exp(-2 pi i k/64)
-// from the table, the rest from short Taylor series of cos and sin of
-// x = 2 pi d / 64 (|x| <= pi/64, truncation below 2e-11).
-__device__ __forceinline__ float2 expi_neg_turns64(double r64) {
-  const double k = rint(r64);
-  const float x = (float)(r64 - k) * (float)(2.0 * kPi / 64.0);
-  const int ki = (int)k & 63;
-  const float x2 = x * x;
-  const float cs = 1.0f + x2 * (-0.5f + x2 * (1.0f / 24.0f));
-  const float sn = x * (1.0f + x2 * (-1.0f / 6.0f + x2 * (1.0f / 120.0f)));
-  const float2 CS = *(const float2*)kRot.cs[ki];
-  // cos(a+b) - i sin(a+b)
-  return make_float2(CS.x * cs - CS.y * sn, -(CS.y * cs + CS.x * sn));
-}
-
-// The same for r in turns (reduced internally).
-__device__ __forceinline__ float2 expi_neg_turns(double r) {
-  const double q = r - rint(r);
-  return expi_neg_turns64(q * 64.0);
-}
-
 // Host: FP64 twiddle tables of a schedule for every pass after the first
 // (entry i of butterfly k = W^(tw_power(R, i) k) at tw_index(i, k, NS)); forward
 // tables then inverse (conjugate) tables.

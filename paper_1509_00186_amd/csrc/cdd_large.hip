@@ -56,10 +56,13 @@ struct LargeArgs {
   int64_t nsamp, nblocks, item0;
   int32_t nchan, N1, N2, M, nfront, phase_mode, exact_div, taper;
   double f_lo, df, dconst, dm;
-  // full-band mode: band width, chirp function per real-spectrum bin (N + 1 entries)
-  double bw;
+  // full-band mode: Eq. 3's phase at bin j is qb j^2 / (1 + qbeta j) turns; the
+  // chirp function per real-spectrum bin (N + 1 entries), or null to form it in
+  // the row pass
+  double qb, qbeta;
   const float2* hb;
-  int32_t lgn;  // log2(N1 N2)
+  int32_t lgn, lg1;  // log2(N1 N2), log2(N1)
+  float gain;        // relative correction of the transforms' gain (split_gain)
   // fused detection + integration in cols_inv (n_int divides the G columns
   // of a workgroup): P and the t_int outputs per channel, and the partial
   // sums of the groups that straddle two column runs (in p: per item, two
@@ -84,23 +87,34 @@ __device__ __forceinline__ int64_t spec_row(const LargeArgs& a, int k2) {
   return (int64_t)(k2 >> a.lgB) + (int64_t)a.A * (k2 & ((1 << a.lgB) - 1));
 }
 
-// exp(-2 pi i m / M) for M = 2^lg: v = ((m + M/2) mod M) - M/2 is m reduced
-// to [-M/2, M/2), and t = v / M the phase in turns in [-1/2, 1/2).  The
-// conversion of v to FP32 is the only rounding (none up to M = 2^25; beyond,
-// t is the correctly rounded FP32 value, within 2^-26 turns), and the
-// hardware sine and cosine take turns (absolute error about 1.2e-7).
-// Computing the four-step twiddles this way keeps the passes free of table
-// gathers, whose scattered indices (n1 k2) touch a cache line per lane.
-__device__ __forceinline__ float2 expi_pow2(int64_t m, int lg) {
-  const int64_t M = (int64_t)1 << lg;
-  const int v = (int)(((m + (M >> 1)) & (M - 1)) - (M >> 1));  // |v| <= 2^26 for lg <= 27
-  const float t = ldexpf((float)v, -lg);
+// Byte offsets into one item's spectra or samples fit 32 bits (N 8 <= 2^29), so
+// the passes address them through a buffer resource on the item's base: one
+// vector offset per thread and scalar offsets per element, where 64-bit
+// addresses took two to four vector operations each.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t item_rsrc(const void* base, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)bytes, 0x00020000);
+}
+typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float2 bload2(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soff, 0));
+}
+__device__ __forceinline__ void bstore2(__amdgpu_buffer_rsrc_t rs, float2 v, int voff, int soff) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, v), rs, voff, soff, 0);
+}
+
+// exp(-2 pi i v / 2^32): v is a phase shifted up so that its turn fills 32
+// bits (m << (32 - lg) for m / 2^lg turns; whole turns fall off the top, so
+// products and sums may wrap).  Read as a signed number it lies in [-1/2, 1/2)
+// turn, and its conversion to FP32 is the only rounding (none up to lg = 24,
+// correctly rounded beyond).
+__device__ __forceinline__ float2 expi_phase(uint32_t v) {
+  const float t = (float)(int32_t)v * 0x1p-32f;
   return make_float2(__builtin_amdgcn_cosf(t), -__builtin_amdgcn_sinf(t));
 }
 
-__device__ __forceinline__ float2 tw4_fwd(const LargeArgs& a, int64_t m) {
-  return expi_pow2(m, a.lgn);
-}
+// The four-step twiddles W_N^(n1 k2) are formed this way (the hardware sine and
+// cosine take turns; absolute error about 1.2e-7) rather than read from a
+// table, whose scattered indices (n1 k2) touch a cache line per lane.
 
 // ---------------------------------------------------------------------------
 // cols_fwd
@@ -123,38 +137,59 @@ __global__ __launch_bounds__(SC::T * G) void cols_fwd_kernel(const LargeArgs a) 
   const int n1 = (rem % ngrp) * G + g;
   const int c = (int)(item / a.nblocks);
   const int64_t k = item - (int64_t)c * a.nblocks;
-  const int64_t base = k * a.M - a.nfront + n1;
+  constexpr int ES = DT == CDD_CI8 ? 2 : 8;
+  const int64_t start = k * a.M - a.nfront;
+  const int pitch = THREE ? a.N1 * a.A : a.N1;  // samples between successive l (n2 = sa + A l)
+  const int v0 = n1 + a.N1 * sa + tl * pitch;
   float2 v[SC::E];
+  if (start >= 0) {
+    // the resource ends at the data's end: the hardware returns zeros past it
+    const int64_t avail = a.nsamp - start, N = (int64_t)a.N1 * a.N2;
+    const __amdgpu_buffer_rsrc_t rs =
+        item_rsrc((const char*)a.x + ((int64_t)c * a.nsamp + start) * ES,
+                  (avail < N ? (avail > 0 ? avail : 0) : N) * ES);
 #pragma unroll
-  for (int b = 0; b < B0; ++b)
+    for (int b = 0; b < B0; ++b)
 #pragma unroll
-    for (int r = 0; r < R0; ++r) {
-      const int l = tl + SC::T * b + r * (L / R0);
-      const int64_t n2 = THREE ? sa + (int64_t)a.A * l : l;
-      const int64_t ts = base + (int64_t)a.N1 * n2;
-      float2 z = make_float2(0.f, 0.f);
-      if (ts >= 0 && ts < a.nsamp) {
+      for (int r = 0; r < R0; ++r) {
+        const int soff = (SC::T * b + r * (L / R0)) * pitch * ES;
         if constexpr (DT == CDD_CI8) {
-          const short w = ((const short*)a.x)[(int64_t)c * a.nsamp + ts];
-          z = make_float2((float)(signed char)(w & 0xff), (float)(signed char)(w >> 8));
+          const unsigned short w = __builtin_amdgcn_raw_buffer_load_b16(rs, v0 * ES, soff, 0);
+          v[b * R0 + r] = make_float2((float)(signed char)(w & 0xff), (float)(signed char)(w >> 8));
         } else {
-          z = ((const float2*)a.x)[(int64_t)c * a.nsamp + ts];
+          v[b * R0 + r] = bload2(rs, v0 * ES, soff);
         }
       }
-      v[b * R0 + r] = z;
-    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < B0; ++b)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) {
+        const int64_t ts = start + v0 + (SC::T * b + r * (L / R0)) * pitch;
+        float2 z = make_float2(0.f, 0.f);
+        if (ts >= 0 && ts < a.nsamp) {
+          if constexpr (DT == CDD_CI8) {
+            const short w = ((const short*)a.x)[(int64_t)c * a.nsamp + ts];
+            z = make_float2((float)(signed char)(w & 0xff), (float)(signed char)(w >> 8));
+          } else {
+            z = ((const float2*)a.x)[(int64_t)c * a.nsamp + ts];
+          }
+        }
+        v[b * R0 + r] = z;
+      }
+  }
   fft_forward<SC>(v, lds + g * (SC::lds_floats() + 1), a.twc, tl);
-  float2* S = a.S + (item - a.item0) * ((int64_t)a.N1 * a.N2);
+  const int64_t N = (int64_t)a.N1 * a.N2;
+  const __amdgpu_buffer_rsrc_t so = item_rsrc(a.S + (item - a.item0) * N, N * 8);
+  // output kk goes to row kk (sa + A kk) times the twiddle of n1 kk / N (sa kk / N2)
+  const uint32_t ph = THREE ? (uint32_t)sa << (32 - a.lg2) : (uint32_t)n1 << (32 - a.lgn);
 #pragma unroll
   for (int b = 0; b < BL; ++b)
 #pragma unroll
     for (int r = 0; r < RL; ++r) {
-      const int kk = tl + SC::T * b + r * (L / RL);
-      if (THREE)
-        S[(sa + (int64_t)a.A * kk) * a.N1 + n1] =
-            cmul(v[b * RL + r], expi_pow2((int64_t)sa * kk, a.lg2));
-      else
-        S[(int64_t)kk * a.N1 + n1] = cmul(v[b * RL + r], tw4_fwd(a, (int64_t)n1 * kk));
+      const int kc = SC::T * b + r * (L / RL);
+      bstore2(so, cmul(v[b * RL + r], expi_phase(ph * (uint32_t)(tl + kc))), v0 * 8,
+              kc * pitch * 8);
     }
 }
 
@@ -183,32 +218,32 @@ __global__ __launch_bounds__(SC::T * G) void cols_mid_kernel(const LargeArgs a) 
   const int kb = rem / ngrp;
   const int n1 = (rem % ngrp) * G + g;
   // rows l + A kb (l < A) of this item, column n1
-  float2* S = a.S + (item - a.item0) * ((int64_t)a.N1 * a.N2) +
-              (int64_t)L * kb * a.N1 + n1;
+  const __amdgpu_buffer_rsrc_t rs = item_rsrc(
+      a.S + (item - a.item0) * ((int64_t)a.N1 * a.N2) + (int64_t)L * kb * a.N1,
+      (int64_t)L * a.N1 * 8);
+  const int voff = (n1 + tl * a.N1) * 8, pitch = a.N1 * 8;
   float2 v[SC::E];
 #pragma unroll
   for (int b = 0; b < BIN; ++b)
 #pragma unroll
     for (int r = 0; r < RIN; ++r)
-      v[b * RIN + r] = S[(int64_t)(tl + SC::T * b + r * (L / RIN)) * a.N1];
+      v[b * RIN + r] = bload2(rs, voff, (SC::T * b + r * (L / RIN)) * pitch);
   float* my = lds + g * (SC::lds_floats() + 1);
   if (INV)
     fft_inverse<SC>(v, my, a.twm, tl);
   else
     fft_forward<SC>(v, my, a.twm, tl);
+  // twiddle of kk kb / N2 (conjugate), or of n1 (kb + B kk) / N
+  const uint32_t ph = INV ? (uint32_t)kb << (32 - a.lg2) : (uint32_t)n1 << (32 - a.lgn);
 #pragma unroll
   for (int b = 0; b < BOUT; ++b)
 #pragma unroll
     for (int r = 0; r < ROUT; ++r) {
-      const int kk = tl + SC::T * b + r * (L / ROUT);
-      float2 w;
-      if (INV) {
-        w = expi_pow2((int64_t)kk * kb, a.lg2);
-        w.y = -w.y;
-      } else {
-        w = tw4_fwd(a, (int64_t)n1 * (kb + ((int64_t)kk << a.lgB)));
-      }
-      S[(int64_t)kk * a.N1] = cmul(v[b * ROUT + r], w);
+      const int kc = SC::T * b + r * (L / ROUT);
+      const uint32_t kk = (uint32_t)(tl + kc);
+      float2 w = expi_phase(ph * (INV ? kk : (uint32_t)kb + (kk << a.lgB)));
+      if (INV) w.y = -w.y;
+      bstore2(rs, cmul(v[b * ROUT + r], w), voff, kc * pitch);
     }
 }
 
@@ -231,8 +266,8 @@ __device__ __forceinline__ float2 chan_chirp(const LargeArgs& a, double fc, int6
     const double x = beta * sd;
     const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                  : (B * (sd * sd)) * fma(x, x, 1.0 - x);
-    const float2 h = expi_neg_turns(q - rint(q));
-    return make_float2(h.x * g, h.y * g);
+    const float2 h = expi_neg_turns_fp32(q - rint(q));
+    return make_float2(fmaf(h.x, a.gain, h.x) * g, fmaf(h.y, a.gain, h.y) * g);
   }
   const float fcf = (float)fc;
   const float Af = (float)(a.dconst * a.dm) / (fcf * fcf);
@@ -240,20 +275,25 @@ __device__ __forceinline__ float2 chan_chirp(const LargeArgs& a, double fc, int6
   const float q = Af * (f * f) / (fcf + f);
   float sn, cs;
   sincospif(2.0f * q, &sn, &cs);
-  return make_float2(cs * g, -sn * g);
+  return make_float2(fmaf(cs, a.gain, cs) * g, -fmaf(sn, a.gain, sn) * g);
 }
 
-// The chirp functions of one call, per channel in the order the row pass
-// reads them: entry c N + k2 N1 + k1 holds bin i = k2 + N2 k1 of channel c.
+// The chirp functions of one call, per channel and row: row c N2 + k2 holds the
+// bins i = k2 + N2 k1 of channel c.  The row pass's threads hold bins of
+// k1 = j + r N1/R (R the last radix of its forward transform, lgJ = log2(N1/R)),
+// and those of even r and of r + 1 lie side by side (chirp_bin), so that one
+// 16-byte load gives a lane two of them.  N1 and N are powers of two: shifts,
+// not the 64-bit divisions that took most of this kernel's time.
 // With a.cov_fill the same launch also sets a.cov_n coverage entries to 1.
-__global__ __launch_bounds__(256) void chan_chirp_table_kernel(LargeArgs a, int64_t N,
+__global__ __launch_bounds__(256) void chan_chirp_table_kernel(LargeArgs a, int32_t lgJ,
                                                                float2* __restrict__ hb) {
+  const int64_t N = (int64_t)1 << a.lgn;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx < a.cov_n) a.cov_fill[idx] = 1;
   if (idx >= N * a.nchan) return;
-  const int c = (int)(idx / N);
-  const int64_t e = idx - (int64_t)c * N;
-  const int64_t i = e / a.N1 + (int64_t)a.N2 * (e % a.N1);
+  const int c = (int)(idx >> a.lgn);
+  const int e = (int)(idx & (N - 1));
+  const int64_t i = (e >> a.lg1) + ((int64_t)chirp_bin(e & (a.N1 - 1), lgJ) << a.lg2);
   const double fc = a.f_lo + ((double)c + 0.5) * a.df;
   hb[idx] = chan_chirp(a, fc, i, N);
 }
@@ -261,6 +301,22 @@ __global__ __launch_bounds__(256) void chan_chirp_table_kernel(LargeArgs a, int6
 // ---------------------------------------------------------------------------
 // rows: forward row DFT, chirp, inverse row DFT, conjugate four-step twiddle
 // ---------------------------------------------------------------------------
+// Results of a row to its place, times the conjugate twiddle of n1 k2 / N.
+template <class SR>
+__device__ __forceinline__ void row_store(const float2* v, __amdgpu_buffer_rsrc_t rs, int voff,
+                                          const LargeArgs& a, int k2, int tl) {
+  constexpr int L = SR::N, R0 = SR::rad_f(0), B0 = L / (R0 * SR::T);
+  const uint32_t ph = (uint32_t)k2 << (32 - a.lgn);
+#pragma unroll
+  for (int b = 0; b < B0; ++b)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const int nc = SR::T * b + r * (L / R0);
+      const float2 w = expi_phase(ph * (uint32_t)(tl + nc));
+      bstore2(rs, cmul(v[b * R0 + r], make_float2(w.x, -w.y)), voff, nc * 8);
+    }
+}
+
 template <class SR, int G>
 __global__ __launch_bounds__(SR::T * G) void rows_kernel(const LargeArgs a) {
   __shared__ float lds[G * (SR::lds_floats() + 1)];
@@ -272,30 +328,30 @@ __global__ __launch_bounds__(SR::T * G) void rows_kernel(const LargeArgs a) {
   const int k2 = (blockIdx.x % ngrp) * G + g;
   const int c = (int)(item / a.nblocks);
   const int64_t N = (int64_t)a.N1 * a.N2;
-  float2* row = a.S + (item - a.item0) * N + spec_row(a, k2) * a.N1;
+  const __amdgpu_buffer_rsrc_t rs = item_rsrc(a.S + (item - a.item0) * N, N * 8);
+  const int voff = ((int)spec_row(a, k2) * L + tl) * 8;
   float2 v[SR::E];
 #pragma unroll
   for (int b = 0; b < B0; ++b)
 #pragma unroll
-    for (int r = 0; r < R0; ++r) v[b * R0 + r] = row[tl + SR::T * b + r * (L / R0)];
+    for (int r = 0; r < R0; ++r) v[b * R0 + r] = bload2(rs, voff, (SR::T * b + r * (L / R0)) * 8);
   float* my = lds + g * (SR::lds_floats() + 1);
   fft_forward<SR>(v, my, a.twr, tl);
-  // chirp on bins i = k2 + N2 k1, from the call's table
-  const float2* h = a.hb + (int64_t)c * N + (int64_t)k2 * a.N1;
+  // chirp on bins i = k2 + N2 k1, from the call's table, two per load
+  const __amdgpu_buffer_rsrc_t hs = item_rsrc(a.hb + (int64_t)c * N, N * 8);
+  const int hoff = k2 * L * 8 + tl * 16;
 #pragma unroll
   for (int b = 0; b < BL; ++b)
 #pragma unroll
-    for (int r = 0; r < RL; ++r)
-      v[b * RL + r] = cmul(v[b * RL + r], h[tl + SR::T * b + r * (L / RL)]);
-  fft_inverse<SR>(v, my, a.twr, tl);
-#pragma unroll
-  for (int b = 0; b < B0; ++b)
-#pragma unroll
-    for (int r = 0; r < R0; ++r) {
-      const int n1 = tl + SR::T * b + r * (L / R0);
-      const float2 w = tw4_fwd(a, (int64_t)n1 * k2);
-      row[n1] = cmul(v[b * R0 + r], make_float2(w.x, -w.y));
+    for (int r = 0; r < RL; r += 2) {
+      const float4 w = __builtin_bit_cast(
+          float4, __builtin_amdgcn_raw_buffer_load_b128(
+                      hs, hoff, ((r >> 1) * (L / RL) + SR::T * b) * 16, 0));
+      v[b * RL + r] = cmul(v[b * RL + r], make_float2(w.x, w.y));
+      v[b * RL + r + 1] = cmul(v[b * RL + r + 1], make_float2(w.z, w.w));
     }
+  fft_inverse<SR>(v, my, a.twr, tl);
+  row_store<SR>(v, rs, voff, a, k2, tl);
 }
 
 // ---------------------------------------------------------------------------
@@ -305,7 +361,11 @@ __global__ __launch_bounds__(SR::T * G) void rows_kernel(const LargeArgs a) {
 // a + A kb give the samples n2 = a + A b.
 template <class SC, int G, bool THREE>
 __global__ __launch_bounds__(SC::T * G) void cols_inv_kernel(const LargeArgs a) {
-  __shared__ float lds[G * (SC::lds_floats() + 1)];
+  // run pitch of the detected samples in LDS; columns above 512 points have no
+  // room for the pad beside a second workgroup
+  constexpr int QP = SC::N <= 512 ? G + 4 : G;
+  constexpr int LDSF = G * (SC::lds_floats() + 1);
+  __shared__ __align__(16) float lds[LDSF > QP * SC::N ? LDSF : QP * SC::N];
   constexpr int L = SC::N, RI = SC::rad_i(0), BI = L / (RI * SC::T);
   constexpr int R0 = SC::rad_f(0), B0 = L / (R0 * SC::T);
   const int t = threadIdx.x, g = t % G, tl = t / G;
@@ -318,86 +378,104 @@ __global__ __launch_bounds__(SC::T * G) void cols_inv_kernel(const LargeArgs a) 
   const int n1 = (rem % ngrp) * G + g;
   const int c = (int)(item / a.nblocks);
   const int64_t k = item - (int64_t)c * a.nblocks;
-  const float2* S = a.S + (item - a.item0) * ((int64_t)a.N1 * a.N2);
+  const int64_t N = (int64_t)a.N1 * a.N2;
+  const __amdgpu_buffer_rsrc_t rs = item_rsrc(a.S + (item - a.item0) * N, N * 8);
+  const int pitch = a.N1 * sA;  // columns between successive local indices
+  const int v0 = n1 + a.N1 * sa + tl * pitch;
   float2 v[SC::E];
 #pragma unroll
   for (int b = 0; b < BI; ++b)
 #pragma unroll
-    for (int r = 0; r < RI; ++r) {
-      const int kk = tl + SC::T * b + r * (L / RI);
-      v[b * RI + r] = S[(sa + (int64_t)sA * kk) * a.N1 + n1];
-    }
+    for (int r = 0; r < RI; ++r)
+      v[b * RI + r] = bload2(rs, v0 * 8, (SC::T * b + r * (L / RI)) * pitch * 8);
   fft_inverse<SC>(v, lds + g * (SC::lds_floats() + 1), a.twc, tl);
+  // sample m = n - nfront of the block's window is kept if 0 <= m < lim; with
+  // the voltages' resource ending at lim, stores outside the window fall away
+  // (a negative m is past the end as an unsigned offset)
+  const int64_t left = a.nsamp - k * a.M;
+  const int lim = (int)(left < a.M ? left : a.M);
+  const int m0 = v0 - a.nfront;
+  const int64_t o0 = (int64_t)c * a.nsamp + k * a.M;
+  if (a.vout) {
+    const __amdgpu_buffer_rsrc_t vs = item_rsrc(a.vout + o0, (int64_t)lim * 8);
+#pragma unroll
+    for (int b = 0; b < B0; ++b)
+#pragma unroll
+      for (int r = 0; r < R0; ++r)
+        bstore2(vs, v[b * R0 + r], (m0 + (SC::T * b + r * (L / R0)) * pitch) * 8, 0);
+  }
   if (!a.fuse) {
 #pragma unroll
     for (int b = 0; b < B0; ++b)
 #pragma unroll
       for (int r = 0; r < R0; ++r) {
-        const int64_t n2 = sa + (int64_t)sA * (tl + SC::T * b + r * (L / R0));
-        const int64_t n = n1 + (int64_t)a.N1 * n2;
-        const int64_t m = n - a.nfront;
-        const int64_t o = k * a.M + m;
-        if (m >= 0 && m < a.M && o < a.nsamp) {
-          const float2 z = v[b * R0 + r];
-          a.p[(int64_t)c * a.nsamp + o] = z.x * z.x + z.y * z.y;
-          if (a.vout) a.vout[(int64_t)c * a.nsamp + o] = z;
-        }
+        const int m = m0 + (SC::T * b + r * (L / R0)) * pitch;
+        const float2 z = v[b * R0 + r];
+        if ((unsigned)m < (unsigned)lim) a.p[o0 + m] = z.x * z.x + z.y * z.y;
       }
     return;
   }
   // Fused detection and integration.  The workgroup holds, for each of its
   // n2, the run of G consecutive samples n = n1b + N1 n2 + g (g < G).  |z|^2
-  // of the kept samples goes to LDS as [local n2][g]; groups of n_int start where
-  // n = nfront (mod n_int).  Groups inside a run are summed here and stored;
-  // a group split across the end of one run and the start of the next is
-  // left as two partial sums for integrate_fixup_kernel.
+  // of the kept samples goes to LDS as [local n2][g], QP words a run (a pad of
+  // four words spreads the runs over the banks and keeps them 16-byte
+  // aligned); groups of n_int start where n = nfront (mod n_int).  Groups
+  // inside a run are summed here and stored; a group split across the end of
+  // one run and the start of the next is left as two partial sums for
+  // integrate_fixup_kernel.
   __syncthreads();  // the transform's last LDS reads are done
   float* q = lds;
 #pragma unroll
   for (int b = 0; b < B0; ++b)
 #pragma unroll
     for (int r = 0; r < R0; ++r) {
-      const int nl = tl + SC::T * b + r * (L / R0);
-      const int64_t n = n1 + (int64_t)a.N1 * (sa + (int64_t)sA * nl);
-      const int64_t m = n - a.nfront;
-      const int64_t o = k * a.M + m;
+      const int nc = SC::T * b + r * (L / R0);
       const float2 z = v[b * R0 + r];
-      const bool kept = m >= 0 && m < a.M && o < a.nsamp;
-      if (kept && a.vout) a.vout[(int64_t)c * a.nsamp + o] = z;
-      q[nl * G + g] = kept ? z.x * z.x + z.y * z.y : 0.f;
+      const bool kept = (unsigned)(m0 + nc * pitch) < (unsigned)lim;
+      q[(tl + nc) * QP + g] = kept ? z.x * z.x + z.y * z.y : 0.f;
     }
   __syncthreads();
-  const int ni = a.n_int;
-  const int phi = (int)(a.nfront % ni);
-  const int per_run = G / ni;  // group starts per run
+  const int ni = a.n_int;                          // a power of two, at most G
+  const int phi = a.nfront & (ni - 1);
+  const int per_run = G / ni;                      // group starts per run
+  const int lgr = 31 - __builtin_clz(per_run);
   const int n1b = n1 - g;
   const int64_t item_local = item - a.item0;
-  float* part = a.p + item_local * ((int64_t)a.N1 * a.N2 / G) * 2;
-  float* Pc = a.P + (int64_t)c * a.t_int;
-  for (int j = threadIdx.x; j < L * (per_run + 1); j += SC::T * G) {
-    const int nl = j / (per_run + 1), slot = j - nl * (per_run + 1);
-    const float* run = q + nl * G;
-    const int64_t n0 = n1b + (int64_t)a.N1 * (sa + (int64_t)sA * nl);  // run's first sample
-    const int64_t ridx = n0 / G;                   // run index in the block
-    if (slot == per_run) {
-      // partial sums: the head [0, phi) and the tail [G - ni + phi, G)
-      if (phi == 0) continue;
+  float* part = a.p + item_local * (N / G) * 2;
+  float* Pu = a.P + (int64_t)c * a.t_int + k * a.M / ni;  // n_int divides M
+  const int64_t ul = a.t_int - k * a.M / ni;
+  const int ulim = (int)(ul < a.M / ni ? ul : a.M / ni);
+  for (int j = threadIdx.x; j < (L << lgr); j += SC::T * G) {
+    const int nl = j >> lgr, slot = j & (per_run - 1);
+    const float* run = q + nl * QP;
+    const int n0 = n1b + a.N1 * (sa + sA * nl);    // run's first sample
+    const int s0 = phi + slot * ni;                // group start within the run
+    if (s0 + ni > G) {
+      // the split group: partial sums of the head [0, phi) and the tail [G - ni + phi, G)
       float h = 0.f, t = 0.f;
       for (int i = 0; i < phi; ++i) h += run[i];
       for (int i = G - ni + phi; i < G; ++i) t += run[i];
-      part[2 * ridx] = h;
-      part[2 * ridx + 1] = t;
+      part[2 * (n0 / G)] = h;
+      part[2 * (n0 / G) + 1] = t;
       continue;
     }
-    const int s0 = phi + slot * ni;  // group start within the run
-    if (s0 + ni > G) continue;       // the split group (partials above)
-    const int64_t m = n0 + s0 - a.nfront;
-    if (m < 0 || m >= a.M) continue;
-    const int64_t u = (k * a.M + m) / ni;
-    if (u >= a.t_int) continue;
+    const int m = n0 + s0 - a.nfront;              // a multiple of n_int
+    if (m < 0) continue;
+    const int u = m / ni;
+    if (u >= ulim) continue;
     float acc = 0.f;
-    for (int i = 0; i < ni; ++i) acc += run[s0 + i];
-    Pc[u] = acc;
+    if ((ni & 3) == 0 && (phi & 3) == 0) {
+      for (int i = 0; i < ni; i += 4) {
+        const float4 x = *(const float4*)(run + s0 + i);
+        acc += x.x;
+        acc += x.y;
+        acc += x.z;
+        acc += x.w;
+      }
+    } else {
+      for (int i = 0; i < ni; ++i) acc += run[s0 + i];
+    }
+    Pu[u] = acc;
   }
 }
 
@@ -496,35 +574,47 @@ static int launch_fixup(const LargeArgs& a, int G, int64_t items, hipStream_t st
 // mirror N - i in row N2 - k2 at k1' = N1 - 1 - k1 (row 0: k1' = -k1 mod N1),
 // so one workgroup transforms rows k2 and N2 - k2 together and hands each
 // row to the other through LDS.
-__device__ __forceinline__ float2 tw2_fwd(const LargeArgs& a, int64_t m) {
-  return expi_pow2(m, a.lgn + 1);
+__device__ __forceinline__ float2 tw2_fwd(const LargeArgs& a, uint32_t m) {
+  return expi_phase(m << (31 - a.lgn));  // m / 2N turns
 }
 
 // Chirp of Eq. 3 about the lower band edge at real-spectrum bin j (0 .. N):
-// f = j bw / N above f_lo, q = D DM f^2 / (f_lo^2 (f_lo + f)) = B j^2 /
-// (1 + beta j) turns in FP64, reduced before the FP32 rotation; times the
-// band taper at x = j/N - 1/2 and the 1/N of the inverse transform.
-__device__ __forceinline__ float2 band_chirp(const LargeArgs& a, double B, double beta,
-                                             int64_t j, float inv_n) {
+// f = j bw / N above f_lo, q = D DM f^2 / (f_lo^2 (f_lo + f)) = qb j^2 /
+// (1 + qbeta j) turns in FP64, reduced before the FP32 rotation; times the
+// band taper at x = j/N - 1/2 and the 1/N of the inverse transform.  The
+// quotient (1 + qbeta j lies in [1, 3)) takes the hardware's reciprocal, two
+// Newton steps and one correction of the quotient itself.
+__device__ __forceinline__ float2 band_chirp(const LargeArgs& a, uint32_t j, float inv_n) {
   const double s = (double)j;
-  const double q = (B * (s * s)) / fma(beta, s, 1.0);
-  const float2 h = expi_neg_turns(q);
+  const double num = a.qb * (s * s), den = fma(a.qbeta, s, 1.0);
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(r, fma(-den, r, 1.0), r);
+  r = fma(r, fma(-den, r, 1.0), r);
+  double q = num * r;
+  q = fma(r, fma(-den, q, num), q);
+  const float2 h = expi_neg_turns_fp32(q - rint(q));
   const float g = inv_n * taper_gain<false>(a.taper, (float)j * inv_n - 0.5f);
-  return make_float2(h.x * g, h.y * g);
+  return make_float2(fmaf(h.x, a.gain, h.x) * g, fmaf(h.y, a.gain, h.y) * g);
 }
 
 // The chirp function of one call for every real-spectrum bin, shared by all
 // blocks of the record, in the order the row pass reads it: entry
-// k2 N1 + k1 holds bin j = k2 + N2 k1 (j < N), entry N the Nyquist bin.
-__global__ __launch_bounds__(256) void band_chirp_table_kernel(LargeArgs a, int64_t N,
+// k2 N1 + k1 holds bin j = k2 + N2 k1 (j < N), entry N the Nyquist bin.  Two
+// neighbouring entries per store, IT of those per thread.  (N1 is a power of
+// two: shifts, not 64-bit divisions.)
+template <int IT>
+__global__ __launch_bounds__(256) void band_chirp_table_kernel(LargeArgs a,
                                                                float2* __restrict__ hb) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx > N) return;
-  const int64_t j = idx == N ? N : idx / a.N1 + (int64_t)a.N2 * (idx % a.N1);
-  const double dfn = a.bw / (double)N;
-  const double B = a.dconst * a.dm * dfn * dfn / (a.f_lo * a.f_lo * a.f_lo);
-  const double beta = dfn / a.f_lo;
-  hb[idx] = band_chirp(a, B, beta, j, 1.0f / (float)N);
+  const uint32_t N = 1u << a.lgn;
+  const float inv_n = 1.0f / (float)N;
+  for (int i = 0; i < IT; ++i) {
+    const uint32_t e = ((blockIdx.x * IT + i) * 256 + threadIdx.x) * 2;
+    if (e >= N) break;
+    const uint32_t j = (e >> a.lg1) + ((e & (uint32_t)(a.N1 - 1)) << a.lg2);
+    const float2 p = band_chirp(a, j, inv_n), q = band_chirp(a, j + (uint32_t)a.N2, inv_n);
+    *(float4*)(hb + e) = make_float4(p.x, p.y, q.x, q.y);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) hb[N] = band_chirp(a, N, inv_n);
 }
 
 template <int L, int LDSF>
@@ -536,7 +626,7 @@ constexpr int pair_stride() {
 // the filtered Z'_i and Z'_(N-i).  With E' = (Y_i + conj Y_(N-i)) / 2 and
 // O' = (Y_i - conj Y_(N-i)) conj(w^i) / 2, Z'_i = E' + i O' and
 // Z'_(N-i) = conj(E') + i conj(O').
-__device__ __forceinline__ void real_pair(const LargeArgs& a, int64_t i, float2 hp, float2 hm,
+__device__ __forceinline__ void real_pair(const LargeArgs& a, uint32_t i, float2 hp, float2 hm,
                                           float2 z, float2 zm, float2* zi, float2* zmi) {
   const float2 e = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));
   const float2 o = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));
@@ -555,7 +645,8 @@ __device__ __forceinline__ void real_pair(const LargeArgs& a, int64_t i, float2 
   *zmi = make_float2(e2.x + o2.y, o2.x - e2.y);
 }
 
-template <class SR, int G>
+// FLY: the chirp is formed here instead of being read from the call's table.
+template <class SR, int G, bool FLY>
 __global__ __launch_bounds__(SR::T * G) void rows_real_kernel(const LargeArgs a) {
   constexpr int L = SR::N, STRIDE = pair_stride<SR::N, SR::lds_floats()>();
   __shared__ __align__(16) float lds[G * STRIDE];
@@ -569,12 +660,13 @@ __global__ __launch_bounds__(SR::T * G) void rows_real_kernel(const LargeArgs a)
   const int side = g & 1;
   const int k2 = pair == 0 ? side * (a.N2 / 2) : (side ? a.N2 - pair : pair);
   const int64_t N = (int64_t)a.N1 * a.N2;
-  float2* row = a.S + (item - a.item0) * N + spec_row(a, k2) * a.N1;
+  const __amdgpu_buffer_rsrc_t rs = item_rsrc(a.S + (item - a.item0) * N, N * 8);
+  const int voff = ((int)spec_row(a, k2) * L + tl) * 8;
   float2 v[SR::E];
 #pragma unroll
   for (int b = 0; b < B0; ++b)
 #pragma unroll
-    for (int r = 0; r < R0; ++r) v[b * R0 + r] = row[tl + SR::T * b + r * (L / R0)];
+    for (int r = 0; r < R0; ++r) v[b * R0 + r] = bload2(rs, voff, (SR::T * b + r * (L / R0)) * 8);
   float* my = lds + g * STRIDE;
   fft_forward<SR>(v, my, a.twr, tl);
   __syncthreads();  // every read of the last exchange is done
@@ -594,29 +686,57 @@ __global__ __launch_bounds__(SR::T * G) void rows_real_kernel(const LargeArgs a)
   const int kB = pair == 0 ? k2 : a.N2 - pair;
   const float2* hA = a.hb + (int64_t)kA * L;  // chirp of row kA's bins, then row kB's
   const float2* hB = a.hb + (int64_t)kB * L;
-  const float2 hnyq = a.hb[N];
-  constexpr int half = L / 2;
-#pragma unroll 2
-  for (int p = tl; p < half; p += SR::T) {
-    int k1, k1m;
-    if (pair != 0) {
-      k1 = p + side * half;
-      k1m = L - 1 - k1;
-    } else if (side == 0) {
-      k1 = p;
-      k1m = (L - p) & (L - 1);
+  const float inv_n = 1.0f / (float)N;
+  auto chirp = [&](const float2* h, int row, int k1) {
+    if constexpr (FLY) {
+      (void)h;
+      return band_chirp(a, (uint32_t)row + ((uint32_t)k1 << a.lg2), inv_n);
     } else {
-      k1 = p;
-      k1m = L - 1 - p;
+      return h[k1];
     }
-    float2 zi, zmi;
-    const int64_t i = kA + (int64_t)a.N2 * k1;
-    real_pair(a, i, hA[k1], i == 0 ? hnyq : hB[k1m], rowA[k1], rowB[k1m], &zi, &zmi);
-    rowA[k1] = zi;
-    rowB[k1m] = zmi;
-    if (pair == 0 && side == 0 && p == 0) {
-      real_pair(a, (int64_t)a.N2 * half, hA[half], hA[half], rowA[half], rowA[half], &zi, &zmi);
-      rowA[half] = zi;
+  };
+  constexpr int half = L / 2;
+  if (pair != 0) {
+    // two neighbouring bins and their mirrors per step: 16-byte accesses
+#pragma unroll 2
+    for (int p = 2 * tl; p < half; p += 2 * SR::T) {
+      const int k1 = p + side * half, k1m = L - 2 - k1;  // bins k1, k1 + 1; k1m + 1, k1m
+      float4 h4, m4;
+      if constexpr (FLY) {
+        const float2 p0 = chirp(hA, kA, k1), p1 = chirp(hA, kA, k1 + 1);
+        const float2 q0 = chirp(hB, kB, k1m), q1 = chirp(hB, kB, k1m + 1);
+        h4 = make_float4(p0.x, p0.y, p1.x, p1.y);
+        m4 = make_float4(q0.x, q0.y, q1.x, q1.y);
+      } else {
+        h4 = *(const float4*)(hA + k1);
+        m4 = *(const float4*)(hB + k1m);
+      }
+      const float4 z4 = *(const float4*)(rowA + k1), y4 = *(const float4*)(rowB + k1m);
+      float2 za, zb, ya, yb;
+      real_pair(a, (uint32_t)kA + ((uint32_t)k1 << a.lg2), make_float2(h4.x, h4.y),
+                make_float2(m4.z, m4.w), make_float2(z4.x, z4.y), make_float2(y4.z, y4.w), &za,
+                &yb);
+      real_pair(a, (uint32_t)kA + ((uint32_t)(k1 + 1) << a.lg2), make_float2(h4.z, h4.w),
+                make_float2(m4.x, m4.y), make_float2(z4.z, z4.w), make_float2(y4.x, y4.y), &zb,
+                &ya);
+      *(float4*)(rowA + k1) = make_float4(za.x, za.y, zb.x, zb.y);
+      *(float4*)(rowB + k1m) = make_float4(ya.x, ya.y, yb.x, yb.y);
+    }
+  } else {
+    for (int p = tl; p < half; p += SR::T) {
+      const int k1 = p, k1m = side == 0 ? (L - p) & (L - 1) : L - 1 - p;
+      float2 zi, zmi;
+      const uint32_t i = (uint32_t)kA + ((uint32_t)k1 << a.lg2);
+      // (the mirror of bin 0 is the Nyquist bin, N = row 0 at k1 = N1)
+      const float2 hm = i == 0 ? chirp(a.hb + N - L, 0, L) : chirp(hB, kB, k1m);
+      real_pair(a, i, chirp(hA, kA, k1), hm, rowA[k1], rowB[k1m], &zi, &zmi);
+      rowA[k1] = zi;
+      rowB[k1m] = zmi;
+      if (side == 0 && p == 0) {
+        const float2 hh = chirp(hA, kA, half);
+        real_pair(a, (uint32_t)half << a.lg2, hh, hh, rowA[half], rowA[half], &zi, &zmi);
+        rowA[half] = zi;
+      }
     }
   }
   __syncthreads();
@@ -625,14 +745,7 @@ __global__ __launch_bounds__(SR::T * G) void rows_real_kernel(const LargeArgs a)
 #pragma unroll
     for (int r = 0; r < RL; ++r) v[b * RL + r] = mine[tl + SR::T * b + r * (L / RL)];
   fft_inverse<SR>(v, my, a.twr, tl);  // its first exchange waits for the reads above
-#pragma unroll
-  for (int b = 0; b < B0; ++b)
-#pragma unroll
-    for (int r = 0; r < R0; ++r) {
-      const int n1 = tl + SR::T * b + r * (L / R0);
-      const float2 w = tw4_fwd(a, (int64_t)n1 * k2);
-      row[n1] = cmul(v[b * R0 + r], make_float2(w.x, -w.y));
-    }
+  row_store<SR>(v, rs, voff, a, k2, tl);
 }
 
 // Inverse transform of recorded spectra (Sec. 2.3, 3.1).  Record s holds
@@ -772,6 +885,20 @@ struct Split {
 // mirror-row pairs, so the count stays even.)
 constexpr int rows_per_group(int T) { return T * 8 <= 256 ? 8 : 256 / T; }
 
+// Mean gain of the hardware's sine and cosine over a turn (measured: the mean of
+// sqrt(cos^2 + sin^2) - 1 over 2^24 phases).
+constexpr double kHwRotationGain = -3.23e-8;
+
+// Relative gain correction of a whole transform pair (see gain_correction): its
+// sub-transforms, and one hardware rotation each way per level above the first.
+template <int LGN>
+static float split_gain() {
+  using SP = Split<LGN>;
+  double g = gain_of<typename SP::SC>() + gain_of<typename SP::SR>();
+  if (SP::THREE) g += gain_of<typename SP::SA>();
+  return (float)(g - 2.0 * (SP::THREE ? 2 : 1) * kHwRotationGain);
+}
+
 // Fill the split-dependent fields of a and its sub-transform twiddles.
 template <int LGN>
 static int set_split(LargeArgs& a) {
@@ -785,6 +912,8 @@ static int set_split(LargeArgs& a) {
   a.lgB = SP::LGB;
   a.lg2 = SP::LGA + SP::LGB;
   a.lgn = LGN;
+  a.lg1 = SP::LG1;
+  a.gain = split_gain<LGN>();
   return e;
 }
 
@@ -811,11 +940,16 @@ static int run_passes(const LargeArgs& a, int64_t q, hipStream_t st) {
   if constexpr (SP::THREE)
     hipLaunchKernelGGL((cols_mid_kernel<SA, GA, false>), dim3((unsigned)ga), dim3(SA::T * GA), 0,
                        st, a);
-  if (REAL)
-    hipLaunchKernelGGL((rows_real_kernel<SR, GR>), dim3((unsigned)gr), dim3(SR::T * GR), 0, st,
-                       a);
-  else
+  if constexpr (REAL) {
+    if (a.hb)
+      hipLaunchKernelGGL((rows_real_kernel<SR, GR, false>), dim3((unsigned)gr), dim3(SR::T * GR),
+                         0, st, a);
+    else
+      hipLaunchKernelGGL((rows_real_kernel<SR, GR, true>), dim3((unsigned)gr), dim3(SR::T * GR),
+                         0, st, a);
+  } else {
     hipLaunchKernelGGL((rows_kernel<SR, GR>), dim3((unsigned)gr), dim3(SR::T * GR), 0, st, a);
+  }
   if constexpr (SP::THREE)
     hipLaunchKernelGGL((cols_mid_kernel<SA, GA, true>), dim3((unsigned)ga), dim3(SA::T * GA), 0,
                        st, a);
@@ -866,7 +1000,8 @@ static int launch_large_t(const BeamPlan& p, const void* xt, double dm, float2* 
   a.hb = S + chunk * NP;
   const int64_t nt = (std::max<int64_t>(NP * p.nchan, a.cov_n) + 255) / 256;
   if (nt > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-  hipLaunchKernelGGL(chan_chirp_table_kernel, dim3((unsigned)nt), dim3(256), 0, st, a, NP,
+  constexpr int LGJ = SP::LG1 - (31 - __builtin_clz(SR::rad_f(SR::NP - 1)));
+  hipLaunchKernelGGL(chan_chirp_table_kernel, dim3((unsigned)nt), dim3(256), 0, st, a, LGJ,
                      (float2*)a.hb);
   for (int64_t i0 = 0; i0 < items; i0 += chunk) {
     const int64_t q = std::min(chunk, items - i0);
@@ -938,6 +1073,24 @@ int64_t fullband_chunk_blocks(const FullbandPlan& f) {
   return std::min(f.nblocks, per);
 }
 
+// The row pass forms the chirp itself for records of up to this many blocks:
+// a table costs its writing once and its reading in every block (8 bytes per
+// bin each, beyond the caches for the long transforms), the FP64 phase about
+// 145 clocks per wave of bins, which a pass bound by HBM mostly hides.  At 2^27
+// real points, two blocks: table 255 us and row passes of 319 us each.
+constexpr int64_t kFlyBlocks = 4;
+
+// gain_of the inverse transform of the records (half a transform pair).
+static double gsb_gain(int nchan) {
+  switch (nchan) {
+    case 128: return 0.5 * gain_of<SubSched<128>::type>();
+    case 256: return 0.5 * gain_of<SubSched<256>::type>();
+    case 512: return 0.5 * gain_of<SubSched<512>::type>();
+    case 1024: return 0.5 * gain_of<SubSched<1024>::type>();
+    default: return 0.5 * gain_of<SubSched<2048>::type>();
+  }
+}
+
 template <int LGN>
 static int launch_fullband_t(const FullbandPlan& f, const float* series, float2* S, float* pbuf,
                              float2* hb, float* I, float* vout, void* stream) {
@@ -947,6 +1100,8 @@ static int launch_fullband_t(const FullbandPlan& f, const float* series, float2*
   LargeArgs a{};
   int e = set_split<LGN>(a);
   if (e) return e;
+  // (half of each mirror pair's power takes two more hardware rotations)
+  a.gain = (float)(a.gain + gsb_gain(f.nchan) - kHwRotationGain);
   a.x = series;
   a.S = S;
   a.p = pbuf;
@@ -960,19 +1115,24 @@ static int launch_fullband_t(const FullbandPlan& f, const float* series, float2*
   a.taper = f.taper;
   a.exact_div = 1;
   a.f_lo = f.f_lo;
-  a.bw = f.bw;
   a.df = f.bw;
   a.dconst = f.dconst;
   a.dm = f.dm;
-  a.hb = hb;
   a.P = I;
   a.t_int = f.t_int;
   a.n_int = f.n_int / 2;  // pairs of real samples
   a.fuse = SP::GC % (f.n_int / 2) == 0 ? 1 : 0;
   hipStream_t st = (hipStream_t)stream;
   constexpr int64_t NP = (int64_t)1 << LGN;
-  hipLaunchKernelGGL(band_chirp_table_kernel, dim3((unsigned)((NP + 256) / 256)), dim3(256), 0,
-                     st, a, NP, hb);
+  const double dfn = f.bw / (double)NP;
+  a.qb = f.dconst * f.dm * dfn * dfn / (f.f_lo * f.f_lo * f.f_lo);
+  a.qbeta = dfn / f.f_lo;
+  a.hb = f.nblocks <= kFlyBlocks ? nullptr : hb;
+  if (a.hb) {
+    constexpr int IT = LGN >= 22 ? 4 : 1;
+    hipLaunchKernelGGL(band_chirp_table_kernel<IT>, dim3((unsigned)((NP / 2 + 256 * IT - 1) / (256 * IT))),
+                       dim3(256), 0, st, a, hb);
+  }
   const int64_t chunk = fullband_chunk_blocks(f);
   for (int64_t i0 = 0; i0 < f.nblocks; i0 += chunk) {
     const int64_t q = std::min(chunk, f.nblocks - i0);
