@@ -33,6 +33,7 @@
 
 #include "cdd_fft.h"
 #include "cdd_internal.h"
+#include "cdd_mfma.h"
 
 namespace cdd {
 
@@ -42,13 +43,13 @@ template <int N, int V>
 struct SchedFor;
 template <> struct SchedFor<256, 0> { using type = Sched<256, 64, 4, 4, 4, 4>; };
 template <> struct SchedFor<512, 0> { using type = Sched<512, 64, 8, 8, 8, 1>; };
-template <> struct SchedFor<1024, 0> { using type = Sched<1024, 64, 16, 16, 4, 1>; };
-template <> struct SchedFor<2048, 0> { using type = Sched<2048, 128, 16, 16, 8, 1>; };
+template <> struct SchedFor<1024, 0> { using type = Sched<1024, 64, 16, 16, 4, 1, true, true>; };
+template <> struct SchedFor<2048, 0> { using type = Sched<2048, 128, 16, 16, 8, 1, true, true>; };
 template <> struct SchedFor<4096, 0> { using type = Sched<4096, 128, 16, 16, 16, 1, true, true, 3>; };
 template <> struct SchedFor<4096, 1> { using type = Sched<4096, 256, 16, 16, 16, 1, false, false, 2>; };
 template <> struct SchedFor<4096, 2> { using type = Sched<4096, 256, 16, 16, 16, 1, true, true, 3>; };
 template <> struct SchedFor<4096, 3> { using type = Sched<4096, 256, 16, 16, 16, 1, true, false, 3>; };
-template <> struct SchedFor<8192, 0> { using type = Sched<8192, 256, 16, 16, 32, 1, true, false, 3>; };
+template <> struct SchedFor<8192, 0> { using type = Sched<8192, 256, 16, 16, 32, 1, true, true, 3>; };
 template <> struct SchedFor<8192, 1> { using type = Sched<8192, 512, 16, 16, 16, 2, true, true, 4>; };
 template <> struct SchedFor<8192, 2> { using type = Sched<8192, 512, 16, 16, 16, 2, true, false, 6>; };
 template <> struct SchedFor<8192, 3> { using type = Sched<8192, 512, 16, 16, 16, 2, false, true, 4>; };
@@ -76,6 +77,7 @@ struct BlockArgs {
   float* P;             // P[dmi*p_dm_stride + c*p_stride + u]
   float2* vout;         // vout[c*v_stride + o] or null (single DM only)
   const float2* tw;     // twiddle tables
+  const float2* mf;     // matrix fragments (first pass of 8-bit records)
   const float2* H;      // single DM: chirp table H[c*N + i] (see chirp_table_kernel)
   int64_t x_stride, x_len, load_off;
   int64_t p_stride, p_dm_stride, u_lim;
@@ -337,6 +339,53 @@ __device__ __forceinline__ void load_block(float2* v, const BlockArgs& a, int c,
   }
 }
 
+// The samples of block k of channel c for the first pass on the matrix cores,
+// two bytes each (coordinates and range as load_block).  A lane's columns come
+// in neighbouring pairs: one 4-byte load for two samples where the block starts
+// on a 4-byte boundary and the data do not end inside a pair (a load across the
+// resource's end returns zero for both), else one load per sample.
+template <class S>
+__device__ __forceinline__ void load_samples(unsigned* w, const BlockArgs& a, int c, int64_t k,
+                                             int t) {
+  constexpr int N = S::N, R = S::rad_f(0);
+  using Map = MfMap<S, R>;
+  constexpr int PT = Map::PT;
+  const int n0 = Map::thread_col(t) + Map::thread_r_in(t) * (N / R);
+  const int64_t t0 = k * a.M - a.load_off;
+  if (t0 >= 0) {
+    const int64_t avail = a.x_len - t0;
+    const int nrec = (int)(avail < N ? avail * 2 : (int64_t)N * 2);
+    const char* base = (const char*)a.x + ((int64_t)c * a.x_stride + t0) * 2;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, nrec, 0x00020000);
+    if ((((uintptr_t)base | (unsigned)nrec) & 3u) == 0) {
+#pragma unroll
+      for (int q = 0; q < S::E / PT; q += 2)
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+          const int e = q * PT + i;
+          const unsigned x = __builtin_amdgcn_raw_buffer_load_b32(
+              rs, n0 * 2, (Map::cc(e) + Map::rc_in(e) * (N / R)) * 2, 0);
+          w[e] = x & 0xffffu;
+          w[e + PT] = x >> 16;
+        }
+    } else {
+#pragma unroll
+      for (int e = 0; e < S::E; ++e)
+        w[e] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(
+            rs, n0 * 2, (Map::cc(e) + Map::rc_in(e) * (N / R)) * 2, 0);
+    }
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < S::E; ++e) {
+    const int64_t tt = t0 + n0 + Map::cc(e) + Map::rc_in(e) * (N / R);
+    w[e] = tt >= 0 && tt < a.x_len
+               ? gptr((const unsigned short*)a.x)[(int64_t)c * a.x_stride + tt]
+               : 0u;
+  }
+}
+
 template <class S, bool VOUT>
 __device__ __forceinline__ void epilogue(const float2* v, float* lds, const BlockArgs& a, int c,
                                          int64_t k, int dmi, int t, bool live = true) {
@@ -404,8 +453,15 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
                        a.dm_step != 0.0;
   if (stepped) rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], a.gain, fc, a, t);
   float2 v[S::E];
-  load_block<S, DT>(v, a, c, k, t);
-  fft_forward<S>(v, lds, a.tw, t);
+  if constexpr (DT == CDD_CI8 && mf_schedule<S>()) {
+    unsigned w[S::E];
+    load_samples<S>(w, a, c, k, t);
+    mf_first<S, S::rad_f(0)>(v, w, a.mf, t);
+    mf_forward_rest<S>(v, lds, a.tw, t);
+  } else {
+    load_block<S, DT>(v, a, c, k, t);
+    fft_forward<S>(v, lds, a.tw, t);
+  }
   if constexpr (!MULTI) {
     (void)fc;
     int tt = t;  // opaque copy: keeps per-bin index math next to its use
@@ -803,10 +859,16 @@ static int resident_workgroups(const void* fn, int threads, int64_t* out) {
   return 0;
 }
 
-// What schedule S needs in the arguments: its twiddles and its gain correction.
+// What schedule S needs in the arguments: its twiddles, its gain correction and,
+// for a first pass on the matrix cores, their fragments.
 template <class S>
 static int tables_of(BlockArgs& a) {
-  a.gain = gain_of<S>();
+  const bool matrix = mf_schedule<S>() && a.dtype == CDD_CI8;
+  a.gain = matrix ? gain_of<S, true>() : gain_of<S>();
+  if (matrix) {
+    const int err = cached_table("mfma32", &make_mf_table, &a.mf);
+    if (err) return err;
+  }
   return twiddles_of<S>(&a.tw);
 }
 
@@ -906,38 +968,40 @@ struct TableForm {
   float gain;
 };
 template <int N, int V>
-static TableForm table_form() {
+static TableForm table_form(int dtype) {
   using S = typename SchedFor<N, V>::type;
-  return {S::rad_f(S::NP - 1), gain_of<S>()};
+  return {S::rad_f(S::NP - 1),
+          mf_schedule<S>() && dtype == CDD_CI8 ? gain_of<S, true>() : gain_of<S>()};
 }
-static TableForm table_form_of(int N, int v) {
+static TableForm table_form_of(int N, int v, int dtype) {
   switch (N) {
-    case 256: return table_form<256, 0>();
-    case 512: return table_form<512, 0>();
-    case 1024: return table_form<1024, 0>();
-    case 2048: return table_form<2048, 0>();
-    case 4096: return table_form<4096, 0>();  // 16 16 16 in every variant
+    case 256: return table_form<256, 0>(dtype);
+    case 512: return table_form<512, 0>(dtype);
+    case 1024: return table_form<1024, 0>(dtype);
+    case 2048: return table_form<2048, 0>(dtype);
+    case 4096:  // 16 16 16 in every variant; the others hold 16 points a thread
+      return v == 0 ? table_form<4096, 0>(dtype) : table_form<4096, 1>(dtype);
     case 8192:
       switch (v) {
-        case 1: return table_form<8192, 1>();
-        case 2: return table_form<8192, 2>();
-        case 3: return table_form<8192, 3>();
-        case 4: return table_form<8192, 4>();
-        case 5: return table_form<8192, 5>();
-        default: return table_form<8192, 0>();  // 16 16 32
+        case 1: return table_form<8192, 1>(dtype);
+        case 2: return table_form<8192, 2>(dtype);
+        case 3: return table_form<8192, 3>(dtype);
+        case 4: return table_form<8192, 4>(dtype);
+        case 5: return table_form<8192, 5>(dtype);
+        default: return table_form<8192, 0>(dtype);  // 16 16 32
       }
     default:
       switch (v) {
-        case 2: return table_form<16384, 2>();
-        case 3: return table_form<16384, 3>();
-        default: return table_form<16384, 0>();  // 16 32 32
+        case 2: return table_form<16384, 2>(dtype);
+        case 3: return table_form<16384, 3>(dtype);
+        default: return table_form<16384, 0>(dtype);  // 16 32 32
       }
   }
 }
 
 ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt, int variant) {
   ChirpTableArgs a{};
-  const TableForm f = table_form_of(p.N, variant);
+  const TableForm f = table_form_of(p.N, variant, p.dtype);
   a.lgJ = log2i(p.N / f.radix);
   a.gain = f.gain;
   a.H = (float2*)H;

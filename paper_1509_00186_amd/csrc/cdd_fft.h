@@ -700,9 +700,9 @@ double gain_correction(bool exact_first = false) {
   }
   return -0.5 * lg;
 }
-template <class S>
+template <class S, bool EXACT_FIRST = false>
 float gain_of() {
-  static const float g = (float)gain_correction<S>();
+  static const float g = (float)gain_correction<S>(EXACT_FIRST);
   return g;
 }
 

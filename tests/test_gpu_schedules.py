@@ -49,3 +49,27 @@ def test_chirp_table_of_a_plan_fits_the_kernel_that_reads_it(N, variant, single_
                          nfront=info["nfront"])
         assert rel_l2(plan.I[b][0].cpu().numpy(), o["I"]) <= TOL_I
     plan.close()
+
+
+@pytest.mark.parametrize("N", [4096, 8192, 16384])
+@pytest.mark.parametrize("offset,nsamp_odd,overlap", [(0, 0, 256), (1, 0, 256), (0, 1, 256),
+                                                      (1, 1, 255), (0, 0, 255)])
+def test_first_pass_on_the_matrix_cores_at_any_alignment(N, offset, nsamp_odd, overlap):
+    """Full-scale bytes in one channel, read in place: records on and off a
+    4-byte boundary, of odd and even length, with blocks starting on odd
+    samples (odd step), the last block cut short."""
+    import torch
+    cdd = _cdd()
+    rng = np.random.default_rng(N + 10 * offset + nsamp_odd)
+    nsamp = 2 * N + 100 + nsamp_odd
+    v = rng.choice(np.array([-128, -1, 0, 1, 127], dtype=np.int8), size=(nsamp, 1, 2))
+    buf = torch.zeros(2 * (nsamp + 8), dtype=torch.int8, device="cuda")
+    buf[2 * offset:2 * offset + v.size] = to_dev(v).reshape(-1)
+    d = buf[2 * offset:2 * offset + v.size].view(nsamp, 1, 2)
+    flush("case: matrix first pass N=%d offset=%d nsamp=%d overlap=%d" % (N, offset, nsamp, overlap))
+    g = cdd.dedisperse(d, 330.0, 0.02, 5.0, N, 1, want_chan=True, want_voltages=True,
+                       overlap=overlap, nfront=128)
+    torch.cuda.synchronize()
+    o = O.dedisperse(v, 330.0, 0.02, 5.0, 1, fft_len=N, overlap=overlap, nfront=128,
+                     want_voltages=True)
+    _check({k: g[k].cpu().numpy() for k in ("I", "cov", "P", "y")}, o)
