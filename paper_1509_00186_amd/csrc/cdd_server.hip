@@ -46,7 +46,7 @@ double now_s() {
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-enum SlotState { FREE = 0, PUSHED = 1, TAKEN = 2 };
+enum SlotState { FREE = 0, PUSHED = 1, TAKEN = 2, FILLING = 3 };
 
 struct Slot {
   void* host = nullptr;  // pinned
@@ -59,8 +59,82 @@ struct Slot {
   SlotState state = FREE;
 };
 
+// Copies of pushed blocks into pinned memory, spread over a few threads: one
+// thread's copy (about 20 GB/s) is slower than the link to the GPU and was most
+// of a serving round.  One copy at a time uses the helpers; a push that finds
+// them busy copies alone.
+class CopyPool {
+ public:
+  ~CopyPool() {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      stop_ = true;
+    }
+    cv_.notify_all();
+    for (auto& t : th_) t.join();
+  }
+  void start() {
+    for (int i = 0; i < kHelpers; ++i) th_.emplace_back([this, i] { work(i); });
+  }
+  void copy(char* dst, const char* src, size_t n) {
+    std::unique_lock<std::mutex> one(use_, std::try_to_lock);
+    if (n < kMinBytes || th_.empty() || !one.owns_lock()) {
+      std::memcpy(dst, src, n);
+      return;
+    }
+    const size_t part = (n / (kHelpers + 1) + 4095) & ~(size_t)4095;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      dst_ = dst;
+      src_ = src;
+      n_ = n;
+      part_ = part;
+      left_ = kHelpers;
+      ++round_;
+    }
+    cv_.notify_all();
+    piece(dst, src, n, part, 0);
+    std::unique_lock<std::mutex> lk(mu_);
+    done_.wait(lk, [&] { return left_ == 0; });
+  }
+
+ private:
+  static constexpr int kHelpers = 3;
+  static constexpr size_t kMinBytes = (size_t)1 << 20;
+  static void piece(char* dst, const char* src, size_t n, size_t part, size_t i) {
+    const size_t a = std::min(n, part * i), b = i == kHelpers ? n : std::min(n, part * (i + 1));
+    if (b > a) std::memcpy(dst + a, src + a, b - a);
+  }
+  void work(int i) {
+    std::unique_lock<std::mutex> lk(mu_);
+    uint64_t seen = 0;
+    while (true) {
+      cv_.wait(lk, [&] { return stop_ || round_ != seen; });
+      if (stop_) return;
+      seen = round_;
+      char* dst = dst_;
+      const char* src = src_;
+      const size_t n = n_, part = part_;
+      lk.unlock();
+      piece(dst, src, n, part, (size_t)i + 1);
+      lk.lock();
+      if (--left_ == 0) done_.notify_one();
+    }
+  }
+  std::mutex use_, mu_;
+  std::condition_variable cv_, done_;
+  std::vector<std::thread> th_;
+  bool stop_ = false;
+  uint64_t round_ = 0;
+  int left_ = 0;
+  char* dst_ = nullptr;
+  const char* src_ = nullptr;
+  size_t n_ = 0, part_ = 0;
+};
+
 struct Stream {
   int id = -1;
+  std::mutex push_mu;  // one push at a time, held while the block is copied
   bool closing = false, flushed = false, released = false, releasing = false;
   BeamPlan p;
   StreamGeom g;
@@ -121,6 +195,7 @@ struct cdd_server {
   double t_first = -1, t_last = 0;
   int pending_work = 0;  // pushed blocks not yet completed
   std::string thread_error;
+  cdd::CopyPool pool;
 };
 
 namespace cdd {
@@ -410,7 +485,10 @@ void scheduler(cdd_server* sv) {
       continue;
     }
     sv->cv.notify_all();
-    sv->cv.wait_for(lk, std::chrono::microseconds(200));
+    // completion is polled: often while a batch is in flight
+    bool in_flight = false;
+    for (auto& b : sv->ring) in_flight |= b.busy;
+    sv->cv.wait_for(lk, std::chrono::microseconds(in_flight ? 40 : 200));
   }
   sv->cv.notify_all();
 }
@@ -440,6 +518,7 @@ cdd_status cdd_server_create(const cdd_server_opts* opts, cdd_server** out) {
       if (e == hipSuccess) e = hipMalloc((void**)&sv->ring[i].counter, 256 * kMaxGroups);
     }
     if (e != hipSuccess) return fail(CDD_EDEVICE, "server create: %s", hipGetErrorString(e));
+    sv->pool.start();
     sv->th = std::thread(scheduler, sv.get());
     *out = sv.release();
     clear_error();
@@ -556,7 +635,13 @@ cdd_status cdd_stream_push(cdd_server* sv, int32_t id, const void* host_block, i
   auto it = sv->streams.find(id);
   if (it == sv->streams.end() || it->second->released)
     return fail(CDD_EINVAL, "no open stream %d", id);
-  Stream* s = it->second.get();
+  Stream* s = it->second.get();  // (streams stay in the map until the server goes)
+  // one push of a stream at a time, in the order of their calls; the server
+  // lock is not held while a block is copied, so the scheduler goes on
+  lk.unlock();
+  std::lock_guard<std::mutex> in_order(s->push_mu);
+  lk.lock();
+  if (s->released) return fail(CDD_EINVAL, "no open stream %d", id);
   if (s->closing) return fail(CDD_EINVAL, "stream %d is closed", id);
   if (nsamp < 1 || nsamp > s->max_block)
     return fail(CDD_EINVAL, "block of %lld samples outside [1, %lld]", (long long)nsamp,
@@ -578,10 +663,25 @@ cdd_status cdd_stream_push(cdd_server* sv, int32_t id, const void* host_block, i
   if (free_slot < 0) return fail(CDD_EAGAIN, "stream %d queue full", id);
   Slot& sl = s->slots[free_slot];
   const size_t bytes = (size_t)nsamp * s->p.nchan * s->elem;
-  std::memcpy(sl.host, host_block, bytes);
-  hipError_t e = hipMemcpyAsync(sl.dev, sl.host, bytes, hipMemcpyHostToDevice, sv->h2d);
+  sl.state = FILLING;
+  lk.unlock();
+  // two halves of a large block, so that the first is on its way to the GPU
+  // while the second is copied
+  const size_t half = bytes >= ((size_t)4 << 20) ? (bytes / 2) & ~(size_t)4095 : bytes;
+  hipError_t e = hipSuccess;
+  for (size_t at = 0; at < bytes && e == hipSuccess;) {
+    const size_t n = at == 0 ? half : bytes - at;
+    sv->pool.copy((char*)sl.host + at, (const char*)host_block + at, n);
+    e = hipMemcpyAsync((char*)sl.dev + at, (char*)sl.host + at, n, hipMemcpyHostToDevice,
+                       sv->h2d);
+    at += n;
+  }
   if (e == hipSuccess) e = hipEventRecord(sl.h2d, sv->h2d);
-  if (e != hipSuccess) return fail(CDD_EDEVICE, "push copy: %s", hipGetErrorString(e));
+  lk.lock();
+  if (e != hipSuccess) {
+    sl.state = FREE;
+    return fail(CDD_EDEVICE, "push copy: %s", hipGetErrorString(e));
+  }
   sl.nsamp = nsamp;
   sl.seq = seq;
   if (timeline_push(&s->tl, s->g, seq, nsamp, s->block_len, &sl.zeros) == kPushGap)
