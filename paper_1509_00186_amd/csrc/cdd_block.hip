@@ -38,10 +38,12 @@
 namespace cdd {
 
 // Schedules per length; variant 0 is the default, others are autotuner
-// candidates.
+// candidates.  256 points take 16 lanes of 16 points, four blocks to a wave:
+// one exchange each way where four passes of radix 4 on 64 lanes took three
+// (23 -> 17 us for the 101-channel float record of 40,001 samples).
 template <int N, int V>
 struct SchedFor;
-template <> struct SchedFor<256, 0> { using type = Sched<256, 64, 4, 4, 4, 4>; };
+template <> struct SchedFor<256, 0> { using type = Sched<256, 16, 16, 16, 1, 1, true, true>; };
 template <> struct SchedFor<512, 0> { using type = Sched<512, 64, 8, 8, 8, 1>; };
 template <> struct SchedFor<1024, 0> { using type = Sched<1024, 64, 16, 16, 4, 1, true, true>; };
 template <> struct SchedFor<2048, 0> { using type = Sched<2048, 128, 16, 16, 8, 1, true, true>; };
@@ -166,25 +168,28 @@ __device__ __forceinline__ void apply_chirp(float2* v, double dm, double fc, con
 // so a tile of DM trials forms the per-unit-DM phase of every bin of its
 // channel once per work item, in FP64 with the same expression as
 // apply_chirp at DM = 1, and each trial then costs one FP64 multiply per bin
-// before the same reduction and rotation.  Entry (b R + r) T + t belongs to
-// thread t alone (written and read by it, no barrier needed).
+// before the same reduction and rotation.  Entry e T + t serves
+// element e of thread t; the ng groups of a workgroup (see wg_blocks) share the
+// table and write every ng-th element each.
+template <class S>
+__device__ __forceinline__ double bin_offset(int e, int t) {
+  constexpr int N = S::N, R = S::rad_f(S::NP - 1);
+  const int b = e / R, r = e % R;
+  return (double)(t + S::T * b + r * (N / R) - (2 * r >= R ? N : 0));
+}
+
 template <class S>
 __device__ __forceinline__ void chirp_phase_per_dm(double* qd, double fc, const BlockArgs& a,
-                                                   int t) {
+                                                   int t, int g, int ng) {
   constexpr int N = S::N, R = S::rad_f(S::NP - 1), BPT = N / (R * S::T);
   const double dfn = a.df / (double)N;
   const double B = a.dconst * dfn * dfn / (fc * fc * fc);  // turns per unit DM
   const double beta = dfn / fc;
   const double Bb = B * beta, Bbb = Bb * beta;
-#pragma unroll
-  for (int b = 0; b < BPT; ++b) {
-    const double s0 = (double)(t + S::T * b);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const double sd = s0 + (double)(r * (N / R) - (2 * r >= R ? N : 0));
-      qd[(b * R + r) * S::T + t] = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
-                                               : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
-    }
+  for (int e = g; e < S::E; e += ng) {
+    const double sd = bin_offset<S>(e, t);
+    qd[e * S::T + t] = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
+                                   : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
   }
 }
 
@@ -216,28 +221,24 @@ __device__ __forceinline__ void apply_chirp_dm(float2* v, double dm, const doubl
 // the rounding of the product: after k steps the chirp is off by at most
 // about k 1e-7 (6e-6 relative at the 64th trial of a tile; measured on the
 // 512-channel beam, the intensities of 64 trials differ from 64 one-DM calls
-// by 1.1e-7 relative L2).  Entry (b R + r) T + t belongs to thread t alone,
-// as in chirp_phase_per_dm (whose LDS the table takes).
+// by 1.1e-7 relative L2).  Entries as in chirp_phase_per_dm (whose LDS the
+// table takes).
 // rs[] receives (1 + gain) exp(-2 pi i DM Q) of this thread's bins for the
 // given DM.
 template <class S>
 __device__ __forceinline__ void rotation_table(float2* rs, double dm, float gain, double fc,
-                                               const BlockArgs& a, int t) {
-  constexpr int N = S::N, R = S::rad_f(S::NP - 1), BPT = N / (R * S::T);
+                                               const BlockArgs& a, int t, int g, int ng) {
+  constexpr int N = S::N;
   const double dfn = a.df / (double)N;
   const double B = a.dconst * dm * dfn * dfn / (fc * fc * fc);  // turns
   const double beta = dfn / fc;
   const double Bb = B * beta, Bbb = Bb * beta;
 #pragma unroll 1
-  for (int b = 0; b < BPT; ++b) {
-    const double s0 = (double)(t + S::T * b);
-#pragma unroll 1
-    for (int r = 0; r < R; ++r) {
-      const double sd = s0 + (double)(r * (N / R) - (2 * r >= R ? N : 0));
-      const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
-                                   : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
-      rs[(b * R + r) * S::T + t] = expi_neg_turns_fp64(q - rint(q), 1.0 + (double)gain);
-    }
+  for (int e = g; e < S::E; e += ng) {
+    const double sd = bin_offset<S>(e, t);
+    const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
+                                 : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
+    rs[e * S::T + t] = expi_neg_turns_fp64(q - rint(q), 1.0 + (double)gain);
   }
 }
 
@@ -286,18 +287,28 @@ __device__ __forceinline__ void chirp_from_table(float2* v, const float2* h, int
   }
 }
 
-// Load block k of channel c: sample n of the block is input sample
-// k*M - load_off + n, zero outside [0, x_len).  Blocks that start inside the
+// Load block k = kw + dk of channel c (kw: the wave's first block): sample n of
+// the block is input sample k*M - load_off + n, zero outside [0, x_len).  Blocks that start inside the
 // data read through a buffer resource whose range ends at the data's end, so
 // the hardware returns zeros past it and no per-sample test is needed.
+// Blocks in a wave.  They belong to one channel, so that the buffer resources of
+// its samples and chirp row are uniform in the wave.
+template <class S>
+constexpr int wave_blocks() {
+  return S::T < 64 ? 64 / S::T : 1;
+}
+
 template <class S, int DT>
-__device__ __forceinline__ void load_block(float2* v, const BlockArgs& a, int c, int64_t k, int t) {
+__device__ __forceinline__ void load_block(float2* v, const BlockArgs& a, int c, int64_t kw, int dk,
+                                           int t) {
   constexpr int N = S::N, R = S::rad_f(0), BPT = N / (R * S::T);
   constexpr int ES = DT == CDD_CI8 ? 2 : 8;
-  const int64_t t0 = k * a.M - a.load_off;
+  const int64_t t0 = kw * a.M - a.load_off;
+  const int n0 = t + dk * a.M;  // (dk is 0 where a wave holds one block)
   if (t0 >= 0) {
     const int64_t avail = a.x_len - t0;
-    const int nrec = (int)(avail < N ? avail * ES : (int64_t)N * ES);
+    const int span = N + (wave_blocks<S>() - 1) * a.M;
+    const int nrec = (int)(avail < span ? avail : span) * ES;
     const char* base = (const char*)a.x + ((int64_t)c * a.x_stride + t0) * ES;
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, nrec, 0x00020000);
@@ -307,13 +318,13 @@ __device__ __forceinline__ void load_block(float2* v, const BlockArgs& a, int c,
       for (int r = 0; r < R; ++r) {
         const int soff = (S::T * b + r * (N / R)) * ES;
         if constexpr (DT == CDD_CI8) {
-          const unsigned short w = __builtin_amdgcn_raw_buffer_load_b16(rs, t * ES, soff, 0);
+          const unsigned short w = __builtin_amdgcn_raw_buffer_load_b16(rs, n0 * ES, soff, 0);
           v[b * R + r] = make_float2((float)(signed char)(w & 0xff), (float)(signed char)(w >> 8));
         } else {
           // the whole 64-bit result reinterpreted at once: indexing its two
           // halves separately compiles to a single 32-bit load here
           v[b * R + r] =
-              __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, t * ES, soff, 0));
+              __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, n0 * ES, soff, 0));
         }
       }
     }
@@ -323,8 +334,7 @@ __device__ __forceinline__ void load_block(float2* v, const BlockArgs& a, int c,
   for (int b = 0; b < BPT; ++b) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int n = t + S::T * b + r * (N / R);
-      const int64_t tt = t0 + n;
+      const int64_t tt = t0 + n0 + S::T * b + r * (N / R);
       float2 z = make_float2(0.f, 0.f);
       if (tt >= 0 && tt < a.x_len) {
         if constexpr (DT == CDD_CI8) {
@@ -444,14 +454,17 @@ __device__ __forceinline__ void epilogue(const float2* v, float* lds, const Bloc
 // qd: N doubles of LDS for the per-unit-DM chirp phase (DM tiles with the
 // FP64 phase), or null to form the phase per trial.
 template <class S, int DT, bool MULTI>
-__device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t k, float* lds,
-                                             int t, bool live = true, double* qd = nullptr) {
+__device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t kw, int dk,
+                                             float* lds, int t, bool live = true,
+                                             double* qd = nullptr, int g = 0, int ng = 1) {
+  const int64_t k = kw + dk;
   const double fc = a.f_lo + ((double)c + 0.5) * a.df;
   // evenly spaced DM trials: the step rotations, formed before anything else
-  // holds registers (the entries are this thread's own)
+  // holds registers
   const bool stepped = MULTI && qd != nullptr && a.phase_mode == CDD_PHASE_FP64_REDUCED &&
                        a.dm_step != 0.0;
-  if (stepped) rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], a.gain, fc, a, t);
+  if (stepped) 
+    rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], a.gain, fc, a, t, g, ng);
   float2 v[S::E];
   if constexpr (DT == CDD_CI8 && mf_schedule<S>()) {
     unsigned w[S::E];
@@ -459,7 +472,7 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
     mf_first<S, S::rad_f(0)>(v, w, a.mf, t);
     mf_forward_rest<S>(v, lds, a.tw, t);
   } else {
-    load_block<S, DT>(v, a, c, k, t);
+    load_block<S, DT>(v, a, c, kw, dk, t);
     fft_forward<S>(v, lds, a.tw, t);
   }
   if constexpr (!MULTI) {
@@ -486,7 +499,8 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
       // takes the step rotation
       float2* rs = reinterpret_cast<float2*>(qd);
       step_chirp<S>(X, rs, t);
-      rotation_table<S>(rs, a.dm_step, 0.0f, fc, a, t);
+      if (ng > 1) __syncthreads();  // every group has read the table
+      rotation_table<S>(rs, a.dm_step, 0.0f, fc, a, t, g, ng);
       for (int i = 0; i < a.dms.ndm; ++i) {
         int tt = t;
         asm volatile("" : "+v"(tt));
@@ -498,7 +512,10 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
       }
       return;
     }
-    if (per_dm) chirp_phase_per_dm<S>(qd, fc, a, t);
+    if (per_dm) {
+      chirp_phase_per_dm<S>(qd, fc, a, t, g, ng);
+      if (ng > 1) __syncthreads();
+    }
     for (int i = 0; i < a.dms.ndm; ++i) {
       // Per-bin indices do not depend on the DM; an opaque copy of the
       // thread index keeps the compiler from hoisting them (and holding them
@@ -537,17 +554,59 @@ __device__ __forceinline__ int64_t xcd_item(int64_t w, int64_t total) {
   return x * q + (x < r ? x : r) + slot;
 }
 
-// One workgroup per (channel, block) of one beam.
+// Blocks of one channel that a workgroup transforms side by side.  A schedule
+// of fewer than 64 threads fills its wave.  DM tiles take two, which share the
+// table of chirp phases in LDS: at 2048 points 33 KB per four waves instead of
+// 25 KB per two, so that four waves per SIMD fit instead of three (the trials
+// wait on LDS and barriers, not on one unit: vector ALUs 66% and LDS 52% busy).
+// 64 trials of the 512-channel, 250,000-sample beam: 12.34 -> 11.79 ms per pass.
+template <class S, bool MULTI>
+constexpr int wg_blocks() {
+  return MULTI && qd_in_lds<S>() && S::T >= 64 && S::T <= 128 ? 2 : wave_blocks<S>();
+}
+template <class S, bool MULTI>
+constexpr int wg_threads() {
+  return S::T * wg_blocks<S, MULTI>();
+}
+template <class S, bool MULTI>
+constexpr int wg_waves() {  // waves per SIMD the register budget targets
+  if (!MULTI) return S::MINB;
+  return wg_blocks<S, true>() > wave_blocks<S>() && S::E <= 16 ? 4 : (S::MINB + 1) / 2;
+}
+
+// Unit of work `unit` of beam a: blocks kg G .. kg G + G - 1 of one channel.
+// The last unit of a channel may hold fewer; its spare groups run on the last
+// block without storing anything (they keep the workgroup's barriers in step).
 template <class S, int DT, bool MULTI>
-__global__ __launch_bounds__(S::T, MULTI ? (S::MINB + 1) / 2 : S::MINB) void block_kernel(
+__device__ __forceinline__ void process_unit(const BlockArgs& a, int64_t unit, float* lds, int tid,
+                                             double* qd) {
+  constexpr int G = wg_blocks<S, MULTI>(), W = wave_blocks<S>();
+  const int64_t per = (a.nblocks + G - 1) / G;
+  const int c = (int)(unit / per);
+  const int64_t k0 = (unit - (int64_t)c * per) * G;
+  if constexpr (G == 1) {
+    process_item<S, DT, MULTI>(a, c, k0, 0, lds, tid, true, qd);
+  } else {
+    int g = tid / S::T;
+    const int t = tid - g * S::T;
+    if constexpr (W == 1) g = __builtin_amdgcn_readfirstlane(g);
+    const int left = (int)min(a.nblocks - k0, (int64_t)G);
+    const bool live = g < left;
+    const int kk = live ? g : left - 1;
+    process_item<S, DT, MULTI>(a, c, W == 1 ? k0 + kk : k0, W == 1 ? 0 : kk,
+                               lds + g * S::lds_floats(), t, live, qd, g, G);
+  }
+}
+
+// One workgroup per unit of one beam.
+template <class S, int DT, bool MULTI>
+__global__ __launch_bounds__((wg_threads<S, MULTI>()), (wg_waves<S, MULTI>())) void block_kernel(
     const BlockArgs a) {
-  __shared__ __align__(16) float lds[S::lds_floats()];
+  __shared__ __align__(16) float lds[wg_blocks<S, MULTI>() * S::lds_floats()];
   constexpr bool QD = MULTI && qd_in_lds<S>();
   __shared__ double qd[QD ? S::N : 1];
-  const int64_t item = xcd_item(blockIdx.x, (int64_t)gridDim.x);
-  const int c = (int)(item / a.nblocks);
-  const int64_t k = item - (int64_t)c * a.nblocks;
-  process_item<S, DT, MULTI>(a, c, k, lds, threadIdx.x, true, QD ? qd : nullptr);
+  process_unit<S, DT, MULTI>(a, xcd_item(blockIdx.x, (int64_t)gridDim.x), lds, threadIdx.x,
+                             QD ? qd : nullptr);
 }
 
 // Persistent form for several beams sharing one transform length and sample
@@ -557,10 +616,10 @@ __global__ __launch_bounds__(S::T, MULTI ? (S::MINB + 1) / 2 : S::MINB) void blo
 // taken; beams are listed longest work first.  Every wave leaves the loop
 // once the counter passes the item count.
 template <class S, int DT>
-__global__ __launch_bounds__(S::T, (S::MINB + 1) / 2) void batch_kernel(
+__global__ __launch_bounds__((wg_threads<S, true>()), (wg_waves<S, true>())) void batch_kernel(
     const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total,
     unsigned int* __restrict__ counter) {
-  __shared__ __align__(16) float lds[S::lds_floats()];
+  __shared__ __align__(16) float lds[wg_blocks<S, true>() * S::lds_floats()];
   constexpr bool QD = qd_in_lds<S>();
   __shared__ double qd[QD ? S::N : 1];
   __shared__ unsigned int s_item;
@@ -575,15 +634,12 @@ __global__ __launch_bounds__(S::T, (S::MINB + 1) / 2) void batch_kernel(
     int b = 0;
     while (b + 1 < nbeams && item >= beams[b + 1].item0) ++b;
     const BlockArgs& a = beams[b];
-    const int64_t local = item - a.item0;
-    const int c = (int)(local / a.nblocks);
-    const int64_t k = local - (int64_t)c * a.nblocks;
     // an opaque copy of the thread index per item keeps the compiler from
     // hoisting per-thread index math out of this loop (and holding it in
     // registers across it)
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
-    process_item<S, DT, true>(a, c, k, lds, t, true, QD ? qd : nullptr);
+    process_unit<S, DT, true>(a, item - a.item0, lds, t, QD ? qd : nullptr);
   }
 }
 
@@ -592,17 +648,14 @@ __global__ __launch_bounds__(S::T, (S::MINB + 1) / 2) void batch_kernel(
 // their first item), XCD-aware as block_kernel; each beam's chirp comes from
 // its own table.
 template <class S, int DT>
-__global__ __launch_bounds__(S::T, S::MINB) void multi_single_kernel(
+__global__ __launch_bounds__((wg_threads<S, false>()), S::MINB) void multi_single_kernel(
     const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total) {
-  __shared__ __align__(16) float lds[S::lds_floats()];
+  __shared__ __align__(16) float lds[wg_blocks<S, false>() * S::lds_floats()];
   const int64_t item = xcd_item(blockIdx.x, total);
   int b = 0;
   while (b + 1 < nbeams && item >= beams[b + 1].item0) ++b;
   const BlockArgs& a = beams[b];
-  const int64_t local = item - a.item0;
-  const int c = (int)(local / a.nblocks);
-  const int64_t k = local - (int64_t)c * a.nblocks;
-  process_item<S, DT, false>(a, c, k, lds, threadIdx.x);
+  process_unit<S, DT, false>(a, item - a.item0, lds, threadIdx.x, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -610,10 +663,10 @@ __global__ __launch_bounds__(S::T, S::MINB) void multi_single_kernel(
 // ---------------------------------------------------------------------------
 // Workgroups of kMixT threads; a length whose schedule has T < kMixT threads
 // runs G = kMixT / T transforms side by side, each on its own slice of the
-// LDS.  A unit of work is G consecutive (channel, block) items of one beam;
-// the last unit of a beam may hold fewer items, and its spare transforms run
-// on a valid block without storing anything (they keep the workgroup's
-// barriers in step).  Beams are listed longest work per unit first; the
+// LDS.  A unit of work is G consecutive (channel, block) items of one beam,
+// those of a wave within one channel; spare transforms of a channel's or a
+// beam's end run on a valid block without storing anything (they keep the
+// workgroup's barriers in step).  Beams are listed longest work per unit first; the
 // workgroups pull units from a counter until none are left, and every wave
 // leaves the loop once the counter passes the unit count.
 constexpr int kMixT = 256;
@@ -649,18 +702,24 @@ __device__ __forceinline__ void mix_unit(const BlockArgs& a, int64_t unit, float
   static_assert(G * S::T == kMixT, "schedule threads must divide the workgroup");
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // per-unit opaque copy (see batch_kernel)
-  const int g = tid / S::T, t = tid - g * S::T;
-  const int64_t items = (int64_t)a.nchan * a.nblocks;
-  int64_t item = unit * G + g;
-  const bool live = item < items;
-  if (!live) item = 0;  // a valid block, nothing stored
-  const int c = (int)(item / a.nblocks);
-  const int64_t k = item - (int64_t)c * a.nblocks;
-  float* my = lds + g * S::lds_floats();
+  // a wave holds W blocks of one channel
+  constexpr int W = wave_blocks<S>(), TW = S::T * W;
+  const int gw = __builtin_amdgcn_readfirstlane(tid / TW);
+  const int w = tid / S::T - gw * W, t = tid % S::T;
+  const int64_t per = (a.nblocks + W - 1) / W;
+  int64_t item = unit * (G / W) + gw;
+  const bool valid = item < a.nchan * per;
+  if (!valid) item = 0;  // a valid block, nothing stored
+  const int c = (int)(item / per);
+  const int64_t kw = (item - (int64_t)c * per) * W;
+  const int left = (int)min(a.nblocks - kw, (int64_t)W);
+  const bool live = valid && w < left;
+  const int dk = w < left ? w : left - 1;
+  float* my = lds + (gw * W + w) * S::lds_floats();
   if (MULTI && a.H == nullptr)
-    process_item<S, DT, true>(a, c, k, my, t, live);
+    process_item<S, DT, true>(a, c, kw, dk, my, t, live);
   else
-    process_item<S, DT, false>(a, c, k, my, t, live);
+    process_item<S, DT, false>(a, c, kw, dk, my, t, live);
 }
 
 // MULTI: some beam carries DM trials or generates its one-DM chirp in the
@@ -878,11 +937,12 @@ static int launch_block_t(const BlockArgs& a0, void* stream) {
   BlockArgs a = a0;
   int err = tables_of<S>(a);
   if (err) return err;
-  const int64_t items = (int64_t)a.nchan * a.nblocks;
-  if (items <= 0 || items > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-  dim3 grid((unsigned)items), block(S::T);
-  hipStream_t st = (hipStream_t)stream;
   const bool multi = a.dms.ndm > 1;
+  const int G = multi ? wg_blocks<S, true>() : wg_blocks<S, false>();
+  const int64_t items = (int64_t)a.nchan * ((a.nblocks + G - 1) / G);
+  if (items <= 0 || items > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+  dim3 grid((unsigned)items), block(S::T * G);
+  hipStream_t st = (hipStream_t)stream;
   if (a.dtype == CDD_CI8) {
     if (multi) hipLaunchKernelGGL((block_kernel<S, CDD_CI8, true>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((block_kernel<S, CDD_CI8, false>), grid, block, 0, st, a);
@@ -1045,48 +1105,57 @@ bool batch_variant_ok(int N, int V) {
 
 bool mixed_supported(int N) { return N >= 256 && N <= 8192 && (N & (N - 1)) == 0; }
 
-static int mix_group(int N) {
-  switch (N) {
-    case 256: return kMixT / MixSched<256>::T;
-    case 512: return kMixT / MixSched<512>::T;
-    case 1024: return kMixT / MixSched<1024>::T;
-    case 2048: return kMixT / MixSched<2048>::T;
-    case 4096: return kMixT / MixSched<4096>::T;
-    case 8192: return kMixT / MixSched<8192>::T;
-  }
-  return 0;
-}
-
-// tables_of for the schedule a launch kind runs for (N, V).
-static int launch_tables(int kind, int N, int V, BlockArgs& a) {
+// Calls f with the schedule a launch kind runs for (N, V).
+template <class F>
+static int with_schedule(int kind, int N, int V, F f) {
   if (kind == kLaunchMixed) {
     switch (N) {
-      case 256: return tables_of<MixSched<256>>(a);
-      case 512: return tables_of<MixSched<512>>(a);
-      case 1024: return tables_of<MixSched<1024>>(a);
-      case 2048: return tables_of<MixSched<2048>>(a);
-      case 4096: return tables_of<MixSched<4096>>(a);
-      case 8192: return tables_of<MixSched<8192>>(a);
+      case 256: return f(MixSched<256>{});
+      case 512: return f(MixSched<512>{});
+      case 1024: return f(MixSched<1024>{});
+      case 2048: return f(MixSched<2048>{});
+      case 4096: return f(MixSched<4096>{});
+      case 8192: return f(MixSched<8192>{});
     }
     return (int)hipErrorInvalidValue;
   }
   if (kind == kLaunchBatch && V != 0) {
-    if (N == 4096 && V == 3) return tables_of<SchedFor<4096, 3>::type>(a);
-    if (N == 8192 && V == 1) return tables_of<SchedFor<8192, 1>::type>(a);
-    if (N == 8192 && V == 2) return tables_of<SchedFor<8192, 2>::type>(a);
-    if (N == 16384 && V == 2) return tables_of<SchedFor<16384, 2>::type>(a);
+    if (N == 4096 && V == 3) return f(SchedFor<4096, 3>::type{});
+    if (N == 8192 && V == 1) return f(SchedFor<8192, 1>::type{});
+    if (N == 8192 && V == 2) return f(SchedFor<8192, 2>::type{});
+    if (N == 16384 && V == 2) return f(SchedFor<16384, 2>::type{});
     return (int)hipErrorInvalidValue;
   }
   switch (N) {
-    case 256: return tables_of<SchedFor<256, 0>::type>(a);
-    case 512: return tables_of<SchedFor<512, 0>::type>(a);
-    case 1024: return tables_of<SchedFor<1024, 0>::type>(a);
-    case 2048: return tables_of<SchedFor<2048, 0>::type>(a);
-    case 4096: return tables_of<SchedFor<4096, 0>::type>(a);
-    case 8192: return tables_of<SchedFor<8192, 0>::type>(a);
-    case 16384: return tables_of<SchedFor<16384, 0>::type>(a);
+    case 256: return f(SchedFor<256, 0>::type{});
+    case 512: return f(SchedFor<512, 0>::type{});
+    case 1024: return f(SchedFor<1024, 0>::type{});
+    case 2048: return f(SchedFor<2048, 0>::type{});
+    case 4096: return f(SchedFor<4096, 0>::type{});
+    case 8192: return f(SchedFor<8192, 0>::type{});
+    case 16384: return f(SchedFor<16384, 0>::type{});
   }
   return (int)hipErrorInvalidValue;
+}
+
+// A unit of work: `sets` sets of `blocks` blocks, each set within one channel.
+struct UnitShape {
+  int blocks = 1, sets = 1;
+  int64_t count(int64_t nchan, int64_t nblocks) const {
+    return (nchan * ((nblocks + blocks - 1) / blocks) + sets - 1) / sets;
+  }
+};
+static int unit_shape(int kind, int N, int V, UnitShape* u) {
+  return with_schedule(kind, N, V, [&](auto s) {
+    using S = decltype(s);
+    if (kind == kLaunchMixed) {
+      u->blocks = wave_blocks<S>();
+      u->sets = kMixT / (S::T * wave_blocks<S>());
+    } else {
+      u->blocks = kind == kLaunchBatch ? wg_blocks<S, true>() : wg_blocks<S, false>();
+    }
+    return 0;
+  });
 }
 
 int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int nbeams,
@@ -1104,6 +1173,7 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
   // workgroup runs at once, each N log N per DM trial)
   std::vector<int> order(nbeams);
   std::vector<double> work(nbeams);
+  std::vector<UnitShape> shape(nbeams);
   for (int b = 0; b < nbeams; ++b) {
     const BeamPlan& p = *beams[b].p;
     const int ndm = beams[b].dms.ndm;
@@ -1118,8 +1188,9 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
     }
     if (!h) out.multi = 1;
     order[b] = b;
-    const int G = kind == kLaunchMixed ? mix_group(p.N) : 1;
-    work[b] = (double)G * p.N * std::log2((double)p.N) * (1 + ndm);
+    int err = unit_shape(kind, p.N, out.variant, &shape[b]);
+    if (err) return err;
+    work[b] = (double)shape[b].blocks * shape[b].sets * p.N * std::log2((double)p.N) * (1 + ndm);
   }
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
   int64_t total = 0;
@@ -1128,12 +1199,11 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
     const BeamPlan& p = *beams[b].p;
     ht[i] = make_args(p, beams[b].co, beams[b].xt, beams[b].dms, beams[b].P, nullptr,
                       (const float2*)(H ? H[b] : nullptr));
-    int err = launch_tables(kind, p.N, out.variant, ht[i]);
+    int err = with_schedule(kind, p.N, out.variant,
+                            [&](auto s) { return tables_of<decltype(s)>(ht[i]); });
     if (err) return err;
     ht[i].item0 = total;
-    const int64_t items = (int64_t)p.nchan * beams[b].co.nblocks;
-    const int G = kind == kLaunchMixed ? mix_group(p.N) : 1;
-    total += (items + G - 1) / G;
+    total += shape[b].count(p.nchan, beams[b].co.nblocks);
   }
   if (total > (kind == kLaunchTables ? 0x7fffffffLL : 0xffffffffLL))
     return (int)hipErrorInvalidValue;
@@ -1148,12 +1218,12 @@ static int enqueue_batch_t(const LaunchDesc& d, const void* dev_tab, unsigned in
   using S = typename SchedFor<N, V>::type;
   hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, st, counter);
   int64_t resident = 0;
-  int err = resident_workgroups(reinterpret_cast<const void*>(&batch_kernel<S, DT>), S::T,
-                                &resident);
+  int err = resident_workgroups(reinterpret_cast<const void*>(&batch_kernel<S, DT>),
+                                wg_threads<S, true>(), &resident);
   if (err) return err;
   const int64_t grid = std::min<int64_t>(d.total, resident);
-  hipLaunchKernelGGL((batch_kernel<S, DT>), dim3((unsigned)grid), dim3(S::T), 0, st,
-                     (const BlockArgs*)dev_tab, d.nbeams, d.total, counter);
+  hipLaunchKernelGGL((batch_kernel<S, DT>), dim3((unsigned)grid), dim3(wg_threads<S, true>()),
+                     0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total, counter);
   return (int)hipGetLastError();
 }
 
@@ -1168,11 +1238,11 @@ template <int N>
 static int enqueue_tables_t(const LaunchDesc& d, const void* dev_tab, hipStream_t st) {
   using S = typename SchedFor<N, 0>::type;
   if (d.dtype == CDD_CI8)
-    hipLaunchKernelGGL((multi_single_kernel<S, CDD_CI8>), dim3((unsigned)d.total), dim3(S::T), 0,
-                       st, (const BlockArgs*)dev_tab, d.nbeams, d.total);
+    hipLaunchKernelGGL((multi_single_kernel<S, CDD_CI8>), dim3((unsigned)d.total),
+                       dim3(wg_threads<S, false>()), 0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total);
   else
-    hipLaunchKernelGGL((multi_single_kernel<S, CDD_CF32>), dim3((unsigned)d.total), dim3(S::T),
-                       0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total);
+    hipLaunchKernelGGL((multi_single_kernel<S, CDD_CF32>), dim3((unsigned)d.total),
+                       dim3(wg_threads<S, false>()), 0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total);
   return (int)hipGetLastError();
 }
 
