@@ -53,3 +53,22 @@ def test_trials_of_neighbouring_blocks(N, dms, kind, single_launch):
                              nfront=info["nfront"])
             assert rel_l2(plan.I[b][i].cpu().numpy(), o["I"]) <= TOL_I
     plan.close()
+
+
+@pytest.mark.parametrize("nfront", [32, 30])
+@pytest.mark.parametrize("N", [256, 512, 1024, 2048, 4096, 8192, 16384])
+def test_sums_of_four(N, nfront):
+    """n_int 4 with a leading overlap that is a multiple of four samples (sums
+    between lanes) and one that is not (through LDS); a record that ends inside
+    a block, stored and accumulated."""
+    import torch
+    cdd = _cdd()
+    nchan, fcen, df, dm = 3, 330.0, 0.02, 6.0
+    v = _beam_int8(80 + N, N + N // 3 + 2, nchan, fcen, df * nchan, dm)
+    got, o, info = _run_both(v, fcen, df * nchan, dm, 4, N, overlap=64, nfront=nfront)
+    assert info["fft_len"] == N and info["nfront"] == nfront
+    _check(got, o)
+    g = cdd.dedisperse(to_dev(np.stack([v, v])), fcen, df * nchan, dm, N, 4, npol=2, overlap=64,
+                       nfront=nfront)
+    torch.cuda.synchronize()
+    assert rel_l2(g["I"].cpu().numpy(), 2 * o["I"]) <= TOL_I
