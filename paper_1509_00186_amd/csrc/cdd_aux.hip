@@ -50,13 +50,20 @@ static DelayArgs delay_args(const BeamPlan& p, double dm, int32_t* delays) {
 // int8 pairs (2 bytes per complex sample): 64 samples x 128 channels per
 // workgroup through LDS; each lane moves 8 bytes (4 complex samples) on both
 // the load (along channels) and the store (along time) side.
-// Float pairs: a 64 x 64 tile, one element per lane access.
 // ---------------------------------------------------------------------------
 // With ct.H set, workgroup w < ct.nwg also writes table workgroup w's share
 // of the one-DM chirp table once its tile stores are issued: the table's
 // FP64 arithmetic runs while the memory-bound layout change's traffic is in
 // flight, instead of in a kernel of its own beside it.  With dl.d set, the
 // last workgroup also writes the channel delays.
+__device__ __forceinline__ void table_and_delays(const ChirpTableArgs& ct, const DelayArgs& dl,
+                                                 int l) {
+  if (ct.H != nullptr && blockIdx.x < ct.nwg) chirp_table_part(ct, blockIdx.x, l);
+  if (dl.d != nullptr && blockIdx.x == gridDim.x - 1)
+    for (int c = l; c < dl.nchan; c += 256)
+      dl.d[c] = channel_delay(c, dl.dm, dl.nchan, dl.f_centre, dl.bw, dl.df, dl.dconst, dl.n_int);
+}
+
 __global__ __launch_bounds__(256) void transpose_i8_kernel(const unsigned short* __restrict__ in,
                                                            unsigned short* __restrict__ out,
                                                            int64_t nsamp, int32_t nchan,
@@ -118,80 +125,96 @@ __global__ __launch_bounds__(256) void transpose_i8_kernel(const unsigned short*
         if (ts + q < nsamp) out[(int64_t)cs * ostr + ts + q] = tile[tl + q][c];
     }
   }
-  if (ct.H != nullptr && blockIdx.x < ct.nwg) chirp_table_part(ct, blockIdx.x, l);
-  if (dl.d != nullptr && blockIdx.x == gridDim.x - 1)
-    for (int c = l; c < dl.nchan; c += 256)
-      dl.d[c] = channel_delay(c, dl.dm, dl.nchan, dl.f_centre, dl.bw, dl.df, dl.dconst, dl.n_int);
+  table_and_delays(ct, dl, l);
 }
 
+// Float pairs: tiles of kTileT samples by 64 channels, bound by memory.  101
+// channels of 40,001 samples (65 MB moved): 18.2 us with 64-sample tiles (33 KB
+// of LDS, four workgroups per CU), 14.6 us with 32, which keep twice as many
+// workgroups in different phases.  The chirp table and the delays ride along as
+// above: with them in kernels of their own a pass over that record took 61 us,
+// now 41.
+constexpr int kTileT = 32;
 __global__ __launch_bounds__(256) void transpose_c8_kernel(const float2* __restrict__ in,
                                                            float2* __restrict__ out,
                                                            int64_t nsamp, int32_t nchan,
-                                                           int32_t tiles_c, int64_t ostr) {
-  __shared__ float2 tile[64][65];
+                                                           int32_t tiles_c, int64_t ostr,
+                                                           const ChirpTableArgs ct,
+                                                           const DelayArgs dl) {
+  __shared__ float2 tile[kTileT][65];
   const int64_t bid = blockIdx.x;
   const int c0 = (int)(bid % tiles_c) * 64;
-  const int64_t t0 = (bid / tiles_c) * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < 64; i += 4) {
-    const int64_t ts = t0 + ty + i;
+  const int64_t t0 = (bid / tiles_c) * kTileT;
+  {
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int cs = c0 + tx;
-    if (ts < nsamp && cs < nchan) tile[ty + i][tx] = in[ts * nchan + cs];
+#pragma unroll
+    for (int i = 0; i < kTileT; i += 4) {
+      const int64_t ts = t0 + ty + i;
+      if (ts < nsamp && cs < nchan) tile[ty + i][tx] = in[ts * nchan + cs];
+    }
   }
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 64; i += 4) {
-    const int cs = c0 + ty + i;
+  {
+    const int tx = threadIdx.x % kTileT, ty = threadIdx.x / kTileT;
     const int64_t ts = t0 + tx;
-    if (cs < nchan && ts < nsamp) out[(int64_t)cs * ostr + ts] = tile[tx][ty + i];
+#pragma unroll
+    for (int i = 0; i < 64; i += 256 / kTileT) {
+      const int cs = c0 + ty + i;
+      if (cs < nchan && ts < nsamp) out[(int64_t)cs * ostr + ts] = tile[tx][ty + i];
+    }
   }
+  table_and_delays(ct, dl, threadIdx.x);
+}
+
+// Tiles of the layout change.
+static int64_t transpose_tiles(int32_t dtype, int64_t nsamp, int32_t nchan, int64_t* tiles_c) {
+  const int tc = dtype == CDD_CI8 ? 128 : 64, tt = dtype == CDD_CI8 ? 64 : kTileT;
+  *tiles_c = (nchan + tc - 1) / tc;
+  return *tiles_c * ((nsamp + tt - 1) / tt);
+}
+
+static int launch_tiles(const void* in, void* out, int32_t dtype, int64_t nsamp, int32_t nchan,
+                        int64_t out_stride, const ChirpTableArgs& ct, const DelayArgs& dl,
+                        hipStream_t st) {
+  int64_t tiles_c = 0;
+  const int64_t n = transpose_tiles(dtype, nsamp, nchan, &tiles_c);
+  if (n <= 0 || n > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+  if (dtype == CDD_CI8)
+    hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)n), dim3(256), 0, st,
+                       (const unsigned short*)in, (unsigned short*)out, nsamp, nchan,
+                       (int32_t)tiles_c, (int32_t)(((uintptr_t)in & 7u) == 0), out_stride, ct, dl);
+  else
+    hipLaunchKernelGGL(transpose_c8_kernel, dim3((unsigned)n), dim3(256), 0, st,
+                       (const float2*)in, (float2*)out, nsamp, nchan, (int32_t)tiles_c,
+                       out_stride, ct, dl);
+  return (int)hipGetLastError();
 }
 
 int launch_transpose(const void* in, void* out, int32_t dtype, int64_t nsamp, int32_t nchan,
                      int64_t out_stride, void* stream) {
-  hipStream_t st = (hipStream_t)stream;
-  if (dtype == CDD_CI8) {
-    const int64_t tiles_c = (nchan + 127) / 128, tiles_t = (nsamp + 63) / 64;
-    const int64_t n = tiles_c * tiles_t;
-    if (n <= 0 || n > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)n), dim3(256), 0, st,
-                       (const unsigned short*)in, (unsigned short*)out, nsamp, nchan,
-                       (int32_t)tiles_c, (int32_t)(((uintptr_t)in & 7u) == 0), out_stride,
-                       ChirpTableArgs{}, DelayArgs{});
-  } else {
-    const int64_t tiles_c = (nchan + 63) / 64, tiles_t = (nsamp + 63) / 64;
-    const int64_t n = tiles_c * tiles_t;
-    if (n <= 0 || n > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL(transpose_c8_kernel, dim3((unsigned)n), dim3(256), 0, st,
-                       (const float2*)in, (float2*)out, nsamp, nchan, (int32_t)tiles_c,
-                       out_stride);
-  }
-  return (int)hipGetLastError();
+  return launch_tiles(in, out, dtype, nsamp, nchan, out_stride, ChirpTableArgs{}, DelayArgs{},
+                      (hipStream_t)stream);
 }
 
 bool transpose_chirp_fits(const BeamPlan& p) {
-  if (p.dtype != CDD_CI8 || p.nchan < 2 || !block_supported(p.N)) return false;
-  const int64_t n = (int64_t)((p.nchan + 127) / 128) * ((p.nsamp + 63) / 64);
-  return (int64_t)p.nchan <= n;  // at least one channel's table per workgroup at kpt = N/256
+  if (p.nchan < 2 || !block_supported(p.N)) return false;
+  int64_t tiles_c = 0;
+  // at least one channel's table per workgroup at kpt = N/256
+  return (int64_t)p.nchan <= transpose_tiles(p.dtype, p.nsamp, p.nchan, &tiles_c);
 }
 
 int launch_transpose_chirp(const BeamPlan& p, const void* in, void* out, double dm, void* H,
                            void* stream, int32_t* delays, int variant) {
   if (!transpose_chirp_fits(p) || H == nullptr) return (int)hipErrorInvalidValue;
-  const int64_t tiles_c = (p.nchan + 127) / 128, tiles_t = (p.nsamp + 63) / 64;
-  const int64_t n = tiles_c * tiles_t;
-  if (n > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+  int64_t tiles_c = 0;
+  const int64_t n = transpose_tiles(p.dtype, p.nsamp, p.nchan, &tiles_c);
   // the fewest table entries per thread that the layout change's workgroups cover
   int kpt = 1;
   while ((int64_t)p.nchan * (p.N / (256 * kpt)) > n && 256 * kpt * 2 <= p.N) kpt *= 2;
-  const ChirpTableArgs ct = chirp_table_args(p, dm, H, kpt, variant);
-  const DelayArgs dl = delay_args(p, dm, delays);
-  hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)n), dim3(256), 0, (hipStream_t)stream,
-                     (const unsigned short*)in, (unsigned short*)out, p.nsamp, p.nchan,
-                     (int32_t)tiles_c, (int32_t)(((uintptr_t)in & 7u) == 0), xt_stride(p), ct,
-                     dl);
-  return (int)hipGetLastError();
+  return launch_tiles(in, out, p.dtype, p.nsamp, p.nchan, xt_stride(p),
+                      chirp_table_args(p, dm, H, kpt, variant), delay_args(p, dm, delays),
+                      (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------

@@ -104,7 +104,7 @@ size_t chirp_table_bytes(const BeamPlan& p);
 // (laid out for schedule `variant` of the length, which the kernel that reads
 // it must run: p.variant, or 0 for the launches that run the default schedule)
 int launch_chirp_table(const BeamPlan& p, double dm, void* H, void* stream, int variant);
-// The int8 layout change of a whole record (into [c][xt_stride]) with the
+// The layout change of a whole record (into [c][xt_stride]) with the
 // one-DM chirp table (and, if delays is set, the channel delays at that DM)
 // built by the same kernel; possible when the layout change has at least one
 // workgroup per channel of the table.
