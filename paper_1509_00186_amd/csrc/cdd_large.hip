@@ -74,6 +74,10 @@ struct LargeArgs {
   // three-level transforms: N2 = A B (A = 1 for the two-level form), the
   // twiddles of the length-A sub-transform, and log2 of N2 and B
   int32_t A, lg2, lgB;
+  // three-level transforms: the column classes kb of this launch of the middle
+  // and row passes (see run_passes): un of them from u0, in the full-band mode
+  // with their mirror classes (see mirror_class)
+  int32_t u0, un;
   const float2* twm;
   // one-channel calls: coverage set to 1 by the chirp-table kernel (or null)
   int32_t* cov_fill;
@@ -204,7 +208,14 @@ __global__ __launch_bounds__(SC::T * G) void cols_fwd_kernel(const LargeArgs a) 
 // of rows ka + A kb, times W_N2^(-a kb), into rows a + A kb, before
 // cols_inv_kernel's inverse DFTs over kb.
 // ---------------------------------------------------------------------------
-template <class SC, int G, bool INV>
+// Class m of the full-band mode's launches: classes 2j and 2j + 1 are a mirror
+// pair (kb, B - kb), the first pair the two classes that mirror themselves.
+__device__ __forceinline__ int mirror_class(const LargeArgs& a, int m) {
+  const int B = 1 << a.lgB, j = m >> 1;
+  return j == 0 ? (m & 1) * (B / 2) : m & 1 ? B - j : j;
+}
+
+template <class SC, int G, bool INV, bool REAL>
 __global__ __launch_bounds__(SC::T * G) void cols_mid_kernel(const LargeArgs a) {
   __shared__ float lds[G * (SC::lds_floats() + 1)];
   constexpr int L = SC::N;  // A
@@ -212,10 +223,10 @@ __global__ __launch_bounds__(SC::T * G) void cols_mid_kernel(const LargeArgs a) 
   constexpr int ROUT = INV ? SC::rad_f(0) : SC::rad_f(SC::NP - 1), BOUT = L / (ROUT * SC::T);
   const int t = threadIdx.x, g = t % G, tl = t / G;
   const int ngrp = a.N1 / G;
-  const int nsub = 1 << a.lgB;  // B
+  const int nsub = REAL ? 2 * a.un : a.un;
   const int64_t item = a.item0 + blockIdx.x / ((unsigned)ngrp * nsub);
   const int rem = (int)(blockIdx.x % ((unsigned)ngrp * nsub));
-  const int kb = rem / ngrp;
+  const int kb = REAL ? mirror_class(a, 2 * a.u0 + rem / ngrp) : a.u0 + rem / ngrp;
   const int n1 = (rem % ngrp) * G + g;
   // rows l + A kb (l < A) of this item, column n1
   const __amdgpu_buffer_rsrc_t rs = item_rsrc(
@@ -317,19 +328,22 @@ __device__ __forceinline__ void row_store(const float2* v, __amdgpu_buffer_rsrc_
     }
 }
 
-template <class SR, int G>
+template <class SR, int G, bool THREE>
 __global__ __launch_bounds__(SR::T * G) void rows_kernel(const LargeArgs a) {
   __shared__ float lds[G * (SR::lds_floats() + 1)];
   constexpr int L = SR::N, R0 = SR::rad_f(0), B0 = L / (R0 * SR::T);
   constexpr int RL = SR::rad_f(SR::NP - 1), BL = L / (RL * SR::T);
   const int t = threadIdx.x, g = t / SR::T, tl = t % SR::T;
-  const int ngrp = a.N2 / G;
+  const int ngrp = (THREE ? a.un * a.A : a.N2) / G;
   const int64_t item = a.item0 + blockIdx.x / ngrp;
-  const int k2 = (blockIdx.x % ngrp) * G + g;
+  // (three levels: the rows of a launch's classes, in the order they lie)
+  const int row = (THREE ? a.u0 * a.A : 0) + (blockIdx.x % ngrp) * G + g;
+  const int lgA = a.lg2 - a.lgB;
+  const int k2 = THREE ? (row >> lgA) + ((row & (a.A - 1)) << a.lgB) : row;
   const int c = (int)(item / a.nblocks);
   const int64_t N = (int64_t)a.N1 * a.N2;
   const __amdgpu_buffer_rsrc_t rs = item_rsrc(a.S + (item - a.item0) * N, N * 8);
-  const int voff = ((int)spec_row(a, k2) * L + tl) * 8;
+  const int voff = (row * L + tl) * 8;
   float2 v[SR::E];
 #pragma unroll
   for (int b = 0; b < B0; ++b)
@@ -646,17 +660,23 @@ __device__ __forceinline__ void real_pair(const LargeArgs& a, uint32_t i, float2
 }
 
 // FLY: the chirp is formed here instead of being read from the call's table.
-template <class SR, int G, bool FLY>
+template <class SR, int G, bool FLY, bool THREE>
 __global__ __launch_bounds__(SR::T * G) void rows_real_kernel(const LargeArgs a) {
   constexpr int L = SR::N, STRIDE = pair_stride<SR::N, SR::lds_floats()>();
   __shared__ __align__(16) float lds[G * STRIDE];
   constexpr int R0 = SR::rad_f(0), B0 = L / (R0 * SR::T);
   constexpr int RL = SR::rad_f(SR::NP - 1), BL = L / (RL * SR::T);
   const int t = threadIdx.x, g = t / SR::T, tl = t % SR::T;
-  // N2/2 row pairs per item, G/2 per workgroup: (0, N2/2), then (k, N2 - k)
-  const int ngrp = a.N2 / G;
+  // N2/2 row pairs per item, G/2 per workgroup: (0, N2/2), then (k, N2 - k);
+  // with three levels A pairs per pair of mirror classes
+  const int ngrp = (THREE ? 2 * a.un * a.A : a.N2) / G;
   const int64_t item = a.item0 + blockIdx.x / ngrp;
-  const int pair = (blockIdx.x % ngrp) * (G / 2) + (g >> 1);
+  int pair = (blockIdx.x % ngrp) * (G / 2) + (g >> 1);
+  if constexpr (THREE) {
+    const int lgA = a.lg2 - a.lgB;
+    const int u = a.u0 + (pair >> lgA), ka = pair & (a.A - 1), B = 1 << a.lgB;
+    pair = u ? u + B * ka : ka < a.A / 2 ? B * ka : B / 2 + B * (ka - a.A / 2);
+  }
   const int side = g & 1;
   const int k2 = pair == 0 ? side * (a.N2 / 2) : (side ? a.N2 - pair : pair);
   const int64_t N = (int64_t)a.N1 * a.N2;
@@ -917,10 +937,34 @@ static int set_split(LargeArgs& a) {
   return e;
 }
 
+// The spectra that a run of passes works through stay in the 256 MiB memory-side
+// cache: between HBM-bound passes (4.9 TB/s copied) of 512 MiB each nothing was
+// left of them there.  A launch of passes takes the items, and the middle and row
+// passes of longer transforms the column classes, that fit: 192 MiB where the
+// call's chirp table is read beside them, 256 MiB without one.  Measured per call,
+// against 512 MiB: one channel of 2^25 samples at 2^18 points 525 -> 460 us, at
+// 2^23 points 727 -> 615 us; full band of 2^27 samples at 2^19 points 1.27 -> 1.12
+// ms, at 2^26 points 2.40 -> 2.10 ms, at 2^27 points 2.31 -> 2.15 ms.  (64 and
+// 128 MiB: 539 and 477, 643 and 610 us; 1.38 and 1.16, 2.11 and 2.12, 2.40 and
+// 2.23 ms: small launches end in a nearly empty round of workgroups.)
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+static int64_t cached_bytes(const LargeArgs& a) {
+  return a.hb ? kCacheBytes / 4 * 3 : kCacheBytes;
+}
+// Launches of each pass for one call of `items` items, at most a chunk each.
+static int64_t cached_launches(const LargeArgs& a, int64_t items, int64_t chunk) {
+  const int64_t most = std::max<int64_t>(1, cached_bytes(a) / ((int64_t)a.N1 * a.N2 * 8));
+  const int64_t n = std::min(most, chunk);
+  return (items + n - 1) / n;
+}
+
 // The passes over one chunk of q items (blocks of one or more channels):
 // columns forward, rows (chirp; REAL: the mirror-pair filter of the real
 // series), columns inverse with the kept window, detection and (fused)
-// integration.  GR rows per workgroup.
+// integration.  GR rows per workgroup.  After the first half of a three-level
+// column transform the rows of one class kb (with the mirror pairs of the real
+// series: of kb and B - kb) need no others until the last pass, so the passes in
+// between take as many classes at a time as stay in the cache.
 template <int LGN, int DT, bool REAL, int GR>
 static int run_passes(const LargeArgs& a, int64_t q, hipStream_t st) {
   using SP = Split<LGN>;
@@ -928,31 +972,40 @@ static int run_passes(const LargeArgs& a, int64_t q, hipStream_t st) {
   using SA = typename SP::SA;
   using SR = typename SP::SR;
   constexpr int GC = SP::GC, GA = SP::GA;
-  static_assert(SP::N2 % GR == 0 && (!REAL || GR % 2 == 0), "row groups tile N2");
+  static_assert(SP::N2 % GR == 0 && (!REAL || GR % 2 == 0) && (!SP::THREE || SP::A % GR == 0),
+                "row groups tile N2 and its classes");
   constexpr int GF = REAL ? GC : SP::GW;
-  const int64_t gc = q * SP::A * (SP::N1 / GC), ga = q * SP::B * (SP::N1 / GA);
-  const int64_t gf = q * SP::A * (SP::N1 / GF);
-  const int64_t gr = q * (SP::N2 / GR);
+  constexpr bool TH = SP::THREE;
+  constexpr int NU = !TH ? 1 : REAL ? SP::B / 2 : SP::B;  // classes (or pairs of them)
+  const int64_t gc = q * SP::A * (SP::N1 / GC), gf = q * SP::A * (SP::N1 / GF);
+  const int64_t ga = q * SP::B * (SP::N1 / GA), gr = q * (SP::N2 / GR);
   if (gc > 0x7fffffffLL || gf > 0x7fffffffLL || ga > 0x7fffffffLL || gr > 0x7fffffffLL)
     return (int)hipErrorInvalidValue;
-  hipLaunchKernelGGL((cols_fwd_kernel<SC, GF, DT, SP::THREE>), dim3((unsigned)gf),
-                     dim3(SC::T * GF), 0, st, a);
-  if constexpr (SP::THREE)
-    hipLaunchKernelGGL((cols_mid_kernel<SA, GA, false>), dim3((unsigned)ga), dim3(SA::T * GA), 0,
-                       st, a);
-  if constexpr (REAL) {
-    if (a.hb)
-      hipLaunchKernelGGL((rows_real_kernel<SR, GR, false>), dim3((unsigned)gr), dim3(SR::T * GR),
-                         0, st, a);
-    else
-      hipLaunchKernelGGL((rows_real_kernel<SR, GR, true>), dim3((unsigned)gr), dim3(SR::T * GR),
-                         0, st, a);
-  } else {
-    hipLaunchKernelGGL((rows_kernel<SR, GR>), dim3((unsigned)gr), dim3(SR::T * GR), 0, st, a);
+  hipLaunchKernelGGL((cols_fwd_kernel<SC, GF, DT, TH>), dim3((unsigned)gf), dim3(SC::T * GF), 0,
+                     st, a);
+  const int64_t unit_bytes = q * ((int64_t)SP::N1 * SP::N2 * 8 / NU);
+  const int per = TH ? (int)std::max<int64_t>(1, std::min<int64_t>(NU, cached_bytes(a) / unit_bytes)) : 1;
+  LargeArgs b = a;
+  for (b.u0 = 0; b.u0 < NU; b.u0 += per) {
+    b.un = std::min(per, NU - b.u0);
+    const unsigned na = (unsigned)(ga / NU * b.un), nr = (unsigned)(gr / NU * b.un);
+    if constexpr (TH)
+      hipLaunchKernelGGL((cols_mid_kernel<SA, GA, false, REAL>), dim3(na), dim3(SA::T * GA), 0, st,
+                         b);
+    if constexpr (REAL) {
+      if (a.hb)
+        hipLaunchKernelGGL((rows_real_kernel<SR, GR, false, TH>), dim3(nr), dim3(SR::T * GR), 0,
+                           st, b);
+      else
+        hipLaunchKernelGGL((rows_real_kernel<SR, GR, true, TH>), dim3(nr), dim3(SR::T * GR), 0, st,
+                           b);
+    } else {
+      hipLaunchKernelGGL((rows_kernel<SR, GR, TH>), dim3(nr), dim3(SR::T * GR), 0, st, b);
+    }
+    if constexpr (TH)
+      hipLaunchKernelGGL((cols_mid_kernel<SA, GA, true, REAL>), dim3(na), dim3(SA::T * GA), 0, st,
+                         b);
   }
-  if constexpr (SP::THREE)
-    hipLaunchKernelGGL((cols_mid_kernel<SA, GA, true>), dim3((unsigned)ga), dim3(SA::T * GA), 0,
-                       st, a);
   hipLaunchKernelGGL((cols_inv_kernel<SC, GC, SP::THREE>), dim3((unsigned)gc), dim3(SC::T * GC),
                      0, st, a);
   int e = 0;
@@ -1003,9 +1056,10 @@ static int launch_large_t(const BeamPlan& p, const void* xt, double dm, float2* 
   constexpr int LGJ = SP::LG1 - (31 - __builtin_clz(SR::rad_f(SR::NP - 1)));
   hipLaunchKernelGGL(chan_chirp_table_kernel, dim3((unsigned)nt), dim3(256), 0, st, a, LGJ,
                      (float2*)a.hb);
-  for (int64_t i0 = 0; i0 < items; i0 += chunk) {
-    const int64_t q = std::min(chunk, items - i0);
-    a.item0 = i0;
+  const int64_t nl = cached_launches(a, items, chunk);
+  for (int64_t l = 0; l < nl; ++l) {
+    a.item0 = items * l / nl;
+    const int64_t q = items * (l + 1) / nl - a.item0;
     e = p.dtype == CDD_CI8 ? run_passes<LGN, CDD_CI8, false, GR>(a, q, st)
                            : run_passes<LGN, CDD_CF32, false, GR>(a, q, st);
     if (e) return e;
@@ -1133,10 +1187,10 @@ static int launch_fullband_t(const FullbandPlan& f, const float* series, float2*
     hipLaunchKernelGGL(band_chirp_table_kernel<IT>, dim3((unsigned)((NP / 2 + 256 * IT - 1) / (256 * IT))),
                        dim3(256), 0, st, a, hb);
   }
-  const int64_t chunk = fullband_chunk_blocks(f);
-  for (int64_t i0 = 0; i0 < f.nblocks; i0 += chunk) {
-    const int64_t q = std::min(chunk, f.nblocks - i0);
-    a.item0 = i0;
+  const int64_t nl = cached_launches(a, f.nblocks, fullband_chunk_blocks(f));
+  for (int64_t l = 0; l < nl; ++l) {
+    a.item0 = f.nblocks * l / nl;
+    const int64_t q = f.nblocks * (l + 1) / nl - a.item0;
     if ((e = run_passes<LGN, CDD_CF32, true, GR>(a, q, st))) return e;
   }
   return a.fuse ? 0 : launch_integrate(pbuf, I, f.nsamp / 2, f.t_int, f.n_int / 2, 1, st);

@@ -45,3 +45,14 @@ def test_window_start_against_the_integration_groups(n_int, shift):
     got, o, info = _run_both(v, 610.0, 8.0, 0.05, n_int, N, overlap=L, nfront=512 + shift)
     assert info["nfront"] == 512 + shift
     _check(got, o)
+
+
+def test_more_items_than_a_launch_takes():
+    """Nine blocks of 2^22 points (32 MiB of spectra each) in three channels: two
+    launches of each pass, the second from the middle of a channel."""
+    N, L, nchan = 1 << 22, 4096, 3
+    nsamp = 2 * (N - L) + 777
+    v = np.random.default_rng(22).integers(-100, 101, size=(nsamp, nchan, 2), dtype=np.int8)
+    got, o, info = _run_both(v, 610.0, 24.0, 0.05, 16, N, want_v=False, overlap=L, nfront=L // 2)
+    assert info["nblocks"] == 3
+    _check(got, o)
