@@ -1,6 +1,7 @@
 // Fused per-(channel, block) coherent dedispersion kernel for gfx950.
 //
-// One workgroup owns one overlap-save block of one channel (N <= 16384):
+// One workgroup owns one overlap-save block of one channel (N <= 16384), or a few
+// neighbouring ones (wg_blocks):
 //   load N samples (int8 or float complex) -> FP32 registers
 //   forward FFT: Stockham autosort radix passes, butterflies in registers,
 //                exchanges through LDS (real and imaginary halves in turn)
@@ -11,6 +12,7 @@
 //   inverse FFT: the same passes in reverse radix order, conjugate twiddles;
 //                its first pass consumes the forward result in registers
 //   epilogue:    keep samples [nfront, nfront + M), |y|^2, sum n_int samples
+//                (between lanes for n_int 4, else through LDS)
 //                (optionally also write the dedispersed voltages)
 // With several DM trials the forward spectrum stays in registers and the
 // chirp, inverse transform and epilogue repeat per trial.
