@@ -653,34 +653,37 @@ __global__ __launch_bounds__((wg_threads<S, MULTI>()), (wg_waves<S, MULTI>())) v
 // Persistent form for several beams sharing one transform length and sample
 // type (one instantiation per type: a run-time switch between the two load
 // paths makes the register allocator spill): a grid sized to the machine
-// pulls work items (beam, channel, block) from a counter until all are
-// taken; beams are listed longest work first.  Every wave leaves the loop
+// pulls work items (beam, channel, blocks), `take` at a time, from a counter
+// until all are taken; beams are listed longest work first.  Every wave leaves the loop
 // once the counter passes the item count.
 template <class S, int DT>
 __global__ __launch_bounds__((wg_threads<S, true>()), (wg_waves<S, true>())) void batch_kernel(
-    const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total,
+    const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total, uint32_t take,
     unsigned int* __restrict__ counter) {
   __shared__ __align__(16) float lds[wg_blocks<S, true>() * S::lds_floats()];
   constexpr bool QD = qd_in_lds<S>();
   __shared__ double qd[QD ? S::N : 1];
   __shared__ unsigned int s_item;
   for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(counter, 1u);
+    if (threadIdx.x == 0) s_item = atomicAdd(counter, take);
     __syncthreads();
     // uniform across the workgroup: kept in a scalar register, so the beam's
     // arguments below are scalar loads and stay out of the vector registers
-    const int64_t item = (int64_t)__builtin_amdgcn_readfirstlane(s_item);
-    __syncthreads();
+    int64_t item = (int64_t)__builtin_amdgcn_readfirstlane(s_item);
+    const int64_t end = min(item + (int64_t)take, total);
     if (item >= total) break;
-    int b = 0;
-    while (b + 1 < nbeams && item >= beams[b + 1].item0) ++b;
-    const BlockArgs& a = beams[b];
-    // an opaque copy of the thread index per item keeps the compiler from
-    // hoisting per-thread index math out of this loop (and holding it in
-    // registers across it)
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    process_unit<S, DT, true>(a, item - a.item0, lds, t, QD ? qd : nullptr);
+    for (; item < end; ++item) {
+      __syncthreads();  // s_item is read, the item before is done with the LDS
+      int b = 0;
+      while (b + 1 < nbeams && item >= beams[b + 1].item0) ++b;
+      const BlockArgs& a = beams[b];
+      // an opaque copy of the thread index per item keeps the compiler from
+      // hoisting per-thread index math out of this loop (and holding it in
+      // registers across it)
+      int t = threadIdx.x;
+      asm volatile("" : "+v"(t));
+      process_unit<S, DT, true>(a, item - a.item0, lds, t, QD ? qd : nullptr);
+    }
   }
 }
 
@@ -1215,6 +1218,7 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
   std::vector<int> order(nbeams);
   std::vector<double> work(nbeams);
   std::vector<UnitShape> shape(nbeams);
+  double points = 0;  // of all units, per transform
   for (int b = 0; b < nbeams; ++b) {
     const BeamPlan& p = *beams[b].p;
     const int ndm = beams[b].dms.ndm;
@@ -1244,13 +1248,29 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
                             [&](auto s) { return tables_of<decltype(s)>(ht[i]); });
     if (err) return err;
     ht[i].item0 = total;
-    total += shape[b].count(p.nchan, beams[b].co.nblocks);
+    const int64_t units = shape[b].count(p.nchan, beams[b].co.nblocks);
+    total += units;
+    points += (double)units * shape[b].blocks * shape[b].sets * p.N * (1 + beams[b].dms.ndm);
   }
   if (total > (kind == kLaunchTables ? 0x7fffffffLL : 0xffffffffLL))
     return (int)hipErrorInvalidValue;
   out.total = total;
+  out.unit_points = total > 0 ? points / (double)total : 0.0;
   *d = out;
   return 0;
+}
+
+// Units that a workgroup of the batch kernel takes from the counter at once.  The
+// counter hands out one value per 12 ns, which set the pace of short units (256
+// points, 2 trials, 512 channels x 250,000 samples: 250,000 units, 3.05 ms per
+// pass); a unit takes about 1.1 ns per point and transform.  So many are taken
+// that the counter is asked for half the values it can give, as long as each
+// workgroup still comes back four times, which keeps the end of the launch even:
+// that pass 1.20 ms, 4 trials at 512 points 2.16 -> 1.34, 2 at 1024 points 1.03 ->
+// 0.76; units of 64 trials are taken singly.
+static uint32_t units_at_once(const LaunchDesc& d, int64_t grid) {
+  const double want = std::ceil(22.0 * (double)grid / std::max(1.0, d.unit_points));
+  return (uint32_t)std::max(1.0, std::min({want, 16.0, (double)(d.total / (4 * grid))}));
 }
 
 template <int N, int V, int DT>
@@ -1264,7 +1284,8 @@ static int enqueue_batch_t(const LaunchDesc& d, const void* dev_tab, unsigned in
   if (err) return err;
   const int64_t grid = std::min<int64_t>(d.total, resident);
   hipLaunchKernelGGL((batch_kernel<S, DT>), dim3((unsigned)grid), dim3(wg_threads<S, true>()),
-                     0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total, counter);
+                     0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total, units_at_once(d, grid),
+                     counter);
   return (int)hipGetLastError();
 }
 

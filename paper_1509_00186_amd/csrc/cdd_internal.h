@@ -159,6 +159,7 @@ enum { kLaunchMixed = 0, kLaunchTables = 1, kLaunchBatch = 2 };
 struct LaunchDesc {
   int kind = 0, N = 0, variant = 0, nbeams = 0, multi = 0, dtype = 0;
   int64_t total = 0;  // work units
+  double unit_points = 0;  // points transformed per unit of work (mean), all trials
 };
 bool mixed_supported(int N);
 bool batch_variant_ok(int N, int V);  // schedules the persistent batch kernel has

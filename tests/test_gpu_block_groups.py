@@ -72,3 +72,32 @@ def test_sums_of_four(N, nfront):
                        nfront=nfront)
     torch.cuda.synchronize()
     assert rel_l2(g["I"].cpu().numpy(), 2 * o["I"]) <= TOL_I
+
+
+@pytest.mark.parametrize("kind", ["int8", "complex64"])
+def test_several_units_taken_at_once(kind):
+    """Two beams of many short blocks and two trials each in one persistent launch,
+    whose workgroups take several units at a time (also across the beams' border),
+    against one call per trial.  Both are FP32 transforms of 256 points, within
+    3e-7 of exact intensities each."""
+    import torch
+    cdd = _cdd()
+    fcen, df, dms = 330.0, 0.02, [20.0, 20.5]
+    raw = []
+    for nchan, nsamp in ((64, 260_001), (48, 250_007)):
+        v = torch.from_numpy(np.random.default_rng(nchan).integers(
+            -100, 101, size=(nsamp, nchan, 2), dtype=np.int8)).cuda()
+        raw.append(torch.view_as_complex(v.float()) if kind == "complex64" else v)
+    flush("case: several units at once, %s" % kind)
+    plan = cdd.Plan([dict(voltages=v, f_centre=fcen, bw=df * v.shape[1], dms=dms, n_int=2,
+                          fft_len=256) for v in raw], single_launch=True)
+    plan.execute()
+    torch.cuda.synchronize()
+    for b, v in enumerate(raw):
+        info = plan.info(b)
+        for i, dm in enumerate(dms):
+            g = cdd.dedisperse(v, fcen, df * v.shape[1], dm, 256, 2, overlap=info["overlap"],
+                               nfront=info["nfront"])
+            want = g["I"].cpu().numpy()
+            assert rel_l2(plan.I[b][i].cpu().numpy()[:want.shape[0]], want) <= 1e-6
+    plan.close()
