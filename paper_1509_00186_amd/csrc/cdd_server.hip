@@ -193,13 +193,30 @@ struct cdd_server {
   std::vector<double> lat;
   cdd_server_stats st{};
   double t_first = -1, t_last = 0;
-  int pending_work = 0;  // pushed blocks not yet completed
+  int pending_work = 0;  // blocks admitted by a push and not yet completed
+  int pushing = 0;       // pushes under way (waiting, copying or queueing)
   std::string thread_error;
   cdd::CopyPool pool;
 };
 
 namespace cdd {
 namespace {
+
+// Counts a push for as long as it uses the server (made and ended with the
+// server lock held).
+class PushCount {
+ public:
+  PushCount(cdd_server* sv, std::unique_lock<std::mutex>& lk) : sv_(sv), lk_(lk) { ++sv_->pushing; }
+  ~PushCount() {
+    if (!lk_.owns_lock()) lk_.lock();
+    --sv_->pushing;
+    sv_->cv.notify_all();
+  }
+
+ private:
+  cdd_server* sv_;
+  std::unique_lock<std::mutex>& lk_;
+};
 
 hipError_t free_stream_mem(Stream* s) {
   for (int i = 0; i < 2; ++i) {
@@ -461,7 +478,7 @@ void scheduler(cdd_server* sv) {
   std::unique_lock<std::mutex> lk(sv->mu);
   while (true) {
     reap(sv, false);
-    if (sv->stop && !has_work(sv)) {
+    if (sv->stop && sv->pushing == 0 && !has_work(sv)) {
       bool busy = false;
       for (auto& br : sv->ring) busy |= br.busy;
       if (!busy) break;
@@ -531,9 +548,11 @@ cdd_status cdd_server_create(const cdd_server_opts* opts, cdd_server** out) {
 void cdd_server_destroy(cdd_server* sv) {
   if (!sv) return;
   {
-    std::lock_guard<std::mutex> lk(sv->mu);
+    // pushes that have begun end first: they copy into the streams' memory
+    std::unique_lock<std::mutex> lk(sv->mu);
     sv->stop = true;
     sv->cv.notify_all();
+    sv->cv.wait(lk, [&] { return sv->pushing == 0; });
   }
   if (sv->th.joinable()) sv->th.join();
   (void)hipStreamSynchronize(sv->compute);
@@ -632,15 +651,18 @@ cdd_status cdd_stream_push(cdd_server* sv, int32_t id, const void* host_block, i
                            uint64_t seq) {
   if (!sv || !host_block) return fail(CDD_EINVAL, "NULL argument");
   std::unique_lock<std::mutex> lk(sv->mu);
+  if (sv->stop) return fail(CDD_EINVAL, "server is being destroyed");
   auto it = sv->streams.find(id);
   if (it == sv->streams.end() || it->second->released)
     return fail(CDD_EINVAL, "no open stream %d", id);
   Stream* s = it->second.get();  // (streams stay in the map until the server goes)
+  const PushCount counted(sv, lk);
   // one push of a stream at a time, in the order of their calls; the server
   // lock is not held while a block is copied, so the scheduler goes on
   lk.unlock();
   std::lock_guard<std::mutex> in_order(s->push_mu);
   lk.lock();
+  if (sv->stop) return fail(CDD_EINVAL, "server is being destroyed");
   if (s->released) return fail(CDD_EINVAL, "no open stream %d", id);
   if (s->closing) return fail(CDD_EINVAL, "stream %d is closed", id);
   if (nsamp < 1 || nsamp > s->max_block)
@@ -663,7 +685,9 @@ cdd_status cdd_stream_push(cdd_server* sv, int32_t id, const void* host_block, i
   if (free_slot < 0) return fail(CDD_EAGAIN, "stream %d queue full", id);
   Slot& sl = s->slots[free_slot];
   const size_t bytes = (size_t)nsamp * s->p.nchan * s->elem;
+  // admitted: from here on whoever waits for queued work waits for this block
   sl.state = FILLING;
+  sv->pending_work++;
   lk.unlock();
   // two halves of a large block, so that the first is on its way to the GPU
   // while the second is copied
@@ -680,6 +704,7 @@ cdd_status cdd_stream_push(cdd_server* sv, int32_t id, const void* host_block, i
   lk.lock();
   if (e != hipSuccess) {
     sl.state = FREE;
+    sv->pending_work--;
     return fail(CDD_EDEVICE, "push copy: %s", hipGetErrorString(e));
   }
   sl.nsamp = nsamp;
@@ -691,7 +716,6 @@ cdd_status cdd_stream_push(cdd_server* sv, int32_t id, const void* host_block, i
   if (sv->t_first < 0) sv->t_first = sl.t_arrive;
   sl.state = PUSHED;
   sv->st.blocks_in++;
-  sv->pending_work++;
   sv->cv.notify_all();
   clear_error();
   return CDD_OK;
