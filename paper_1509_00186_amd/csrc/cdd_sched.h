@@ -38,6 +38,27 @@ bool admit(size_t used, size_t budget, int open, int max_streams, size_t bytes);
 enum PushVerdict { kPushNext = 0, kPushGap = 1, kPushStale = 2 };
 PushVerdict classify_push(uint64_t next_seq, uint64_t seq);
 
+// Moves a pushed block into its slot and on to the device, a large one in two
+// halves, the first on its way while the second is copied: stage(at, n) copies n
+// bytes on the host, send(at, n) queues their transfer, mark() records the event
+// behind the last.  Returns the first error, or 0.  After an error the transfers
+// already queued still read the slot, so drain() waits for them before the caller
+// may give the slot to another block.
+template <class Stage, class Send, class Mark, class Drain>
+int fill_slot(size_t bytes, Stage stage, Send send, Mark mark, Drain drain) {
+  const size_t half = bytes >= ((size_t)4 << 20) ? (bytes / 2) & ~(size_t)4095 : bytes;
+  int e = 0;
+  for (size_t at = 0; at < bytes && e == 0;) {
+    const size_t n = at == 0 ? half : bytes - at;
+    stage(at, n);
+    e = send(at, n);
+    at += n;
+  }
+  if (e == 0) e = mark();
+  if (e != 0) drain();
+  return e;
+}
+
 // The timeline of one stream, in absolute samples (per channel) and
 // integrated samples.  Block k of the overlap-save grid reads input samples
 // [k M - nfront, k M - nfront + N) and yields outputs [k M, k M + M).

@@ -689,18 +689,17 @@ cdd_status cdd_stream_push(cdd_server* sv, int32_t id, const void* host_block, i
   sl.state = FILLING;
   sv->pending_work++;
   lk.unlock();
-  // two halves of a large block, so that the first is on its way to the GPU
-  // while the second is copied
-  const size_t half = bytes >= ((size_t)4 << 20) ? (bytes / 2) & ~(size_t)4095 : bytes;
-  hipError_t e = hipSuccess;
-  for (size_t at = 0; at < bytes && e == hipSuccess;) {
-    const size_t n = at == 0 ? half : bytes - at;
-    sv->pool.copy((char*)sl.host + at, (const char*)host_block + at, n);
-    e = hipMemcpyAsync((char*)sl.dev + at, (char*)sl.host + at, n, hipMemcpyHostToDevice,
-                       sv->h2d);
-    at += n;
-  }
-  if (e == hipSuccess) e = hipEventRecord(sl.h2d, sv->h2d);
+  const hipError_t e = (hipError_t)fill_slot(
+      bytes,
+      [&](size_t at, size_t n) {
+        sv->pool.copy((char*)sl.host + at, (const char*)host_block + at, n);
+      },
+      [&](size_t at, size_t n) {
+        return (int)hipMemcpyAsync((char*)sl.dev + at, (char*)sl.host + at, n,
+                                   hipMemcpyHostToDevice, sv->h2d);
+      },
+      [&] { return (int)hipEventRecord(sl.h2d, sv->h2d); },
+      [&] { (void)hipStreamSynchronize(sv->h2d); });
   lk.lock();
   if (e != hipSuccess) {
     sl.state = FREE;
