@@ -1,7 +1,7 @@
 // Fused per-(channel, block) coherent dedispersion kernel for gfx950.
 //
 // One workgroup owns one overlap-save block of one channel (N <= 16384), or a few
-// neighbouring ones (wg_blocks):
+// neighbouring ones (process_unit):
 //   load N samples (int8 or float complex) -> FP32 registers
 //   forward FFT: Stockham autosort radix passes, butterflies in registers,
 //                exchanges through LDS (real and imaginary halves in turn)
@@ -36,6 +36,7 @@
 #include "cdd_fft.h"
 #include "cdd_internal.h"
 #include "cdd_mfma.h"
+#include "cdd_rules.h"
 
 namespace cdd {
 
@@ -171,7 +172,7 @@ __device__ __forceinline__ void apply_chirp(float2* v, double dm, double fc, con
 // channel once per work item, in FP64 with the same expression as
 // apply_chirp at DM = 1, and each trial then costs one FP64 multiply per bin
 // before the same reduction and rotation.  Entry e T + t serves
-// element e of thread t; the ng groups of a workgroup (see wg_blocks) share the
+// element e of thread t; the ng groups of a workgroup (see tile_pairs) share the
 // table and write every ng-th element each.
 template <class S>
 __device__ __forceinline__ double bin_offset(int e, int t) {
@@ -596,32 +597,29 @@ __device__ __forceinline__ int64_t xcd_item(int64_t w, int64_t total) {
 }
 
 // Blocks of one channel that a workgroup transforms side by side.  A schedule
-// of fewer than 64 threads fills its wave.  DM tiles take two, which share the
+// of fewer than 64 threads fills its wave.  DM tiles can take two, which share the
 // table of chirp phases in LDS: at 2048 points 33 KB per four waves instead of
 // 25 KB per two, so that four waves per SIMD fit instead of three (the trials
 // wait on LDS and barriers, not on one unit: vector ALUs 66% and LDS 52% busy).
 // 64 trials of the 512-channel, 250,000-sample beam: 12.34 -> 11.79 ms per pass.
-template <class S, bool MULTI>
-constexpr int wg_blocks() {
-  return MULTI && qd_in_lds<S>() && S::T >= 64 && S::T <= 128 ? 2 : wave_blocks<S>();
+// Whether a launch takes two: two_blocks_pay.
+template <class S>
+constexpr bool tile_pairs() {
+  return qd_in_lds<S>() && S::T >= 64 && S::T <= 128;
 }
-template <class S, bool MULTI>
-constexpr int wg_threads() {
-  return S::T * wg_blocks<S, MULTI>();
-}
-template <class S, bool MULTI>
+template <class S, bool MULTI, int G>
 constexpr int wg_waves() {  // waves per SIMD the register budget targets
   if (!MULTI) return S::MINB;
-  return wg_blocks<S, true>() > wave_blocks<S>() && S::E <= 16 ? 4 : (S::MINB + 1) / 2;
+  return G > wave_blocks<S>() && S::E <= 16 ? 4 : (S::MINB + 1) / 2;
 }
 
 // Unit of work `unit` of beam a: blocks kg G .. kg G + G - 1 of one channel.
 // The last unit of a channel may hold fewer; its spare groups run on the last
 // block without storing anything (they keep the workgroup's barriers in step).
-template <class S, int DT, bool MULTI>
+template <class S, int DT, bool MULTI, int G>
 __device__ __forceinline__ void process_unit(const BlockArgs& a, int64_t unit, float* lds, int tid,
                                              double* qd) {
-  constexpr int G = wg_blocks<S, MULTI>(), W = wave_blocks<S>();
+  constexpr int W = wave_blocks<S>();
   const int64_t per = (a.nblocks + G - 1) / G;
   const int c = (int)(unit / per);
   const int64_t k0 = (unit - (int64_t)c * per) * G;
@@ -641,13 +639,15 @@ __device__ __forceinline__ void process_unit(const BlockArgs& a, int64_t unit, f
 
 // One workgroup per unit of one beam.
 template <class S, int DT, bool MULTI>
-__global__ __launch_bounds__((wg_threads<S, MULTI>()), (wg_waves<S, MULTI>())) void block_kernel(
+__global__ __launch_bounds__(S::T * wave_blocks<S>(),
+                             (wg_waves<S, MULTI, wave_blocks<S>()>())) void block_kernel(
     const BlockArgs a) {
-  __shared__ __align__(16) float lds[wg_blocks<S, MULTI>() * S::lds_floats()];
+  constexpr int G = wave_blocks<S>();
+  __shared__ __align__(16) float lds[G * S::lds_floats()];
   constexpr bool QD = MULTI && qd_in_lds<S>();
   __shared__ double qd[QD ? S::N : 1];
-  process_unit<S, DT, MULTI>(a, xcd_item(blockIdx.x, (int64_t)gridDim.x), lds, threadIdx.x,
-                             QD ? qd : nullptr);
+  process_unit<S, DT, MULTI, G>(a, xcd_item(blockIdx.x, (int64_t)gridDim.x), lds, threadIdx.x,
+                                QD ? qd : nullptr);
 }
 
 // Persistent form for several beams sharing one transform length and sample
@@ -656,11 +656,11 @@ __global__ __launch_bounds__((wg_threads<S, MULTI>()), (wg_waves<S, MULTI>())) v
 // pulls work items (beam, channel, blocks), `take` at a time, from a counter
 // until all are taken; beams are listed longest work first.  Every wave leaves the loop
 // once the counter passes the item count.
-template <class S, int DT>
-__global__ __launch_bounds__((wg_threads<S, true>()), (wg_waves<S, true>())) void batch_kernel(
+template <class S, int DT, int G>
+__global__ __launch_bounds__(S::T * G, (wg_waves<S, true, G>())) void batch_kernel(
     const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total, uint32_t take,
     unsigned int* __restrict__ counter) {
-  __shared__ __align__(16) float lds[wg_blocks<S, true>() * S::lds_floats()];
+  __shared__ __align__(16) float lds[G * S::lds_floats()];
   constexpr bool QD = qd_in_lds<S>();
   __shared__ double qd[QD ? S::N : 1];
   __shared__ unsigned int s_item;
@@ -682,7 +682,7 @@ __global__ __launch_bounds__((wg_threads<S, true>()), (wg_waves<S, true>())) voi
       // registers across it)
       int t = threadIdx.x;
       asm volatile("" : "+v"(t));
-      process_unit<S, DT, true>(a, item - a.item0, lds, t, QD ? qd : nullptr);
+      process_unit<S, DT, true, G>(a, item - a.item0, lds, t, QD ? qd : nullptr);
     }
   }
 }
@@ -692,14 +692,14 @@ __global__ __launch_bounds__((wg_threads<S, true>()), (wg_waves<S, true>())) voi
 // their first item), XCD-aware as block_kernel; each beam's chirp comes from
 // its own table.
 template <class S, int DT>
-__global__ __launch_bounds__((wg_threads<S, false>()), S::MINB) void multi_single_kernel(
+__global__ __launch_bounds__(S::T * wave_blocks<S>(), S::MINB) void multi_single_kernel(
     const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total) {
-  __shared__ __align__(16) float lds[wg_blocks<S, false>() * S::lds_floats()];
+  __shared__ __align__(16) float lds[wave_blocks<S>() * S::lds_floats()];
   const int64_t item = xcd_item(blockIdx.x, total);
   int b = 0;
   while (b + 1 < nbeams && item >= beams[b + 1].item0) ++b;
   const BlockArgs& a = beams[b];
-  process_unit<S, DT, false>(a, item - a.item0, lds, threadIdx.x, nullptr);
+  process_unit<S, DT, false, wave_blocks<S>()>(a, item - a.item0, lds, threadIdx.x, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -982,7 +982,7 @@ static int launch_block_t(const BlockArgs& a0, void* stream) {
   int err = tables_of<S>(a);
   if (err) return err;
   const bool multi = a.dms.ndm > 1;
-  const int G = multi ? wg_blocks<S, true>() : wg_blocks<S, false>();
+  constexpr int G = wave_blocks<S>();
   const int64_t items = (int64_t)a.nchan * ((a.nblocks + G - 1) / G);
   if (items <= 0 || items > 0x7fffffffLL) return (int)hipErrorInvalidValue;
   dim3 grid((unsigned)items), block(S::T * G);
@@ -1189,14 +1189,30 @@ struct UnitShape {
     return (nchan * ((nblocks + blocks - 1) / blocks) + sets - 1) / sets;
   }
 };
-static int unit_shape(int kind, int N, int V, UnitShape* u) {
+static int unit_shape(int kind, int N, int V, bool pairs, UnitShape* u) {
   return with_schedule(kind, N, V, [&](auto s) {
     using S = decltype(s);
-    if (kind == kLaunchMixed) {
-      u->blocks = wave_blocks<S>();
-      u->sets = kMixT / (S::T * wave_blocks<S>());
-    } else {
-      u->blocks = kind == kLaunchBatch ? wg_blocks<S, true>() : wg_blocks<S, false>();
+    u->blocks = pairs ? 2 : wave_blocks<S>();
+    if (kind == kLaunchMixed) u->sets = kMixT / (S::T * wave_blocks<S>());
+    return 0;
+  });
+}
+
+// Whether the units of a batch launch take two blocks each.
+static int paired_blocks(int kind, int V, const BatchBeam* beams, int nbeams, bool* pairs) {
+  *pairs = false;
+  if (kind != kLaunchBatch) return 0;
+  return with_schedule(kind, beams[0].p->N, V, [&](auto s) {
+    if constexpr (tile_pairs<decltype(s)>()) {
+      int64_t blocks = 0, doubled = 0;
+      double trials = 0;
+      for (int b = 0; b < nbeams; ++b) {
+        const int64_t c = beams[b].p->nchan, n = beams[b].co.nblocks;
+        blocks += c * n;
+        doubled += c * ((n + 1) / 2 * 2);
+        trials += (double)(c * n) * beams[b].dms.ndm;
+      }
+      *pairs = blocks > 0 && two_blocks_pay(beams[0].p->N, trials / (double)blocks, blocks, doubled);
     }
     return 0;
   });
@@ -1219,6 +1235,7 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
   std::vector<double> work(nbeams);
   std::vector<UnitShape> shape(nbeams);
   double points = 0;  // of all units, per transform
+  if (int err = paired_blocks(kind, out.variant, beams, nbeams, &out.pairs)) return err;
   for (int b = 0; b < nbeams; ++b) {
     const BeamPlan& p = *beams[b].p;
     const int ndm = beams[b].dms.ndm;
@@ -1233,7 +1250,7 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
     }
     if (!h) out.multi = 1;
     order[b] = b;
-    int err = unit_shape(kind, p.N, out.variant, &shape[b]);
+    int err = unit_shape(kind, p.N, out.variant, out.pairs, &shape[b]);
     if (err) return err;
     work[b] = (double)shape[b].blocks * shape[b].sets * p.N * std::log2((double)p.N) * (1 + ndm);
   }
@@ -1273,20 +1290,27 @@ static uint32_t units_at_once(const LaunchDesc& d, int64_t grid) {
   return (uint32_t)std::max(1.0, std::min({want, 16.0, (double)(d.total / (4 * grid))}));
 }
 
+template <class S, int DT, int G>
+static int enqueue_batch_g(const LaunchDesc& d, const void* dev_tab, unsigned int* counter,
+                           hipStream_t st) {
+  hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, st, counter);
+  int64_t resident = 0;
+  int err = resident_workgroups(reinterpret_cast<const void*>(&batch_kernel<S, DT, G>), S::T * G,
+                                &resident);
+  if (err) return err;
+  const int64_t grid = std::min<int64_t>(d.total, resident);
+  hipLaunchKernelGGL((batch_kernel<S, DT, G>), dim3((unsigned)grid), dim3(S::T * G), 0, st,
+                     (const BlockArgs*)dev_tab, d.nbeams, d.total, units_at_once(d, grid), counter);
+  return (int)hipGetLastError();
+}
+
 template <int N, int V, int DT>
 static int enqueue_batch_t(const LaunchDesc& d, const void* dev_tab, unsigned int* counter,
                            hipStream_t st) {
   using S = typename SchedFor<N, V>::type;
-  hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, st, counter);
-  int64_t resident = 0;
-  int err = resident_workgroups(reinterpret_cast<const void*>(&batch_kernel<S, DT>),
-                                wg_threads<S, true>(), &resident);
-  if (err) return err;
-  const int64_t grid = std::min<int64_t>(d.total, resident);
-  hipLaunchKernelGGL((batch_kernel<S, DT>), dim3((unsigned)grid), dim3(wg_threads<S, true>()),
-                     0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total, units_at_once(d, grid),
-                     counter);
-  return (int)hipGetLastError();
+  if constexpr (tile_pairs<S>())
+    if (d.pairs) return enqueue_batch_g<S, DT, 2>(d, dev_tab, counter, st);
+  return enqueue_batch_g<S, DT, wave_blocks<S>()>(d, dev_tab, counter, st);
 }
 
 template <int N, int V>
@@ -1301,10 +1325,12 @@ static int enqueue_tables_t(const LaunchDesc& d, const void* dev_tab, hipStream_
   using S = typename SchedFor<N, 0>::type;
   if (d.dtype == CDD_CI8)
     hipLaunchKernelGGL((multi_single_kernel<S, CDD_CI8>), dim3((unsigned)d.total),
-                       dim3(wg_threads<S, false>()), 0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total);
+                       dim3(S::T * wave_blocks<S>()), 0, st, (const BlockArgs*)dev_tab, d.nbeams,
+                       d.total);
   else
     hipLaunchKernelGGL((multi_single_kernel<S, CDD_CF32>), dim3((unsigned)d.total),
-                       dim3(wg_threads<S, false>()), 0, st, (const BlockArgs*)dev_tab, d.nbeams, d.total);
+                       dim3(S::T * wave_blocks<S>()), 0, st, (const BlockArgs*)dev_tab, d.nbeams,
+                       d.total);
   return (int)hipGetLastError();
 }
 

@@ -158,6 +158,7 @@ size_t batch_table_bytes(int nbeams);
 enum { kLaunchMixed = 0, kLaunchTables = 1, kLaunchBatch = 2 };
 struct LaunchDesc {
   int kind = 0, N = 0, variant = 0, nbeams = 0, multi = 0, dtype = 0;
+  bool pairs = false; // batch launches: two blocks of a channel per unit
   int64_t total = 0;  // work units
   double unit_points = 0;  // points transformed per unit of work (mean), all trials
 };

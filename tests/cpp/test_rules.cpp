@@ -1,0 +1,51 @@
+// CPU tests of the dispatch rules (cdd_rules.h).
+#include <cstdio>
+
+#include "cdd_rules.h"
+
+using namespace cdd;
+
+static int g_fail = 0;
+#define CHECK(cond)                                                   \
+  do {                                                                \
+    if (!(cond)) {                                                    \
+      std::printf("FAIL %s:%d: %s\n", __FILE__, __LINE__, #cond);     \
+      ++g_fail;                                                       \
+    }                                                                 \
+  } while (0)
+
+static bool two(int N, int trials, int64_t nchan, int64_t n) {
+  return two_blocks_pay(N, trials, nchan * n, nchan * ((n + 1) / 2 * 2));
+}
+
+// Two blocks per workgroup never where the spare ones cost more than sharing gains.
+static void test_two_blocks() {
+  for (int N : {512, 1024, 2048, 4096}) {
+    for (int trials : {1, 2, 3, 8, 16, 32, 64}) {
+      if (N == 4096 && trials <= 4) continue;     // faster throughout
+      CHECK(!two(N, trials, 2048, 1));            // twice the transforms
+      CHECK(two(N, trials, 2048, 2));             // nothing spare
+      CHECK(two(N, trials, 512, 131) && two(N, trials, 512, 33));
+      CHECK(!two(N, trials, 16, 9) && !two(N, trials, 16, 10));  // a compute unit per block
+      bool last = false;  // once two pay at an odd count, they do at every larger one
+      for (int64_t n = 1; n < 200; n += 2) {
+        const bool t = two(N, trials, 1024, n);
+        CHECK(t || !last);
+        last = t;
+      }
+    }
+    CHECK(!two(N, 16, 1024, 3) || N == 512);
+    CHECK(!two(N, 48, 1024, 3));
+    CHECK(!two(N, 48, 1024, 5) || N == 4096);
+  }
+}
+
+int main() {
+  test_two_blocks();
+  if (g_fail) {
+    std::printf("%d failures\n", g_fail);
+    return 1;
+  }
+  std::printf("all passed\n");
+  return 0;
+}
