@@ -6,6 +6,7 @@
 
 #include "cdd_fft.h"
 #include "cdd_internal.h"
+#include "cdd_rules.h"
 
 namespace cdd {
 
@@ -310,11 +311,8 @@ int launch_detect(const BeamPlan& p, const void* xt, float* P, void* stream) {
 // bound by HBM: the record is read once and P written once, where the copy
 // read and wrote the record again (512 channels x 250,000 int8 samples, n_int
 // 4: 92 + 118 us for copy and detection, 76 us here).  NI: n_int at compile
-// time (0: any).  The last workgroup also writes the channel delays.
-// A long integration leaves few outputs, so few workgroups: from
-// kDetectTiledMax samples on the copy and detect_kernel are taken instead.
-constexpr int kDetectTiledMax = 64;
-
+// time (0: any).  The last workgroup also writes the channel delays.  Where the
+// copy and detect_kernel are taken instead: detect_from_record.
 template <int DT, int CPT, int NI>
 __global__ __launch_bounds__(256) void detect_tiled_kernel(const void* __restrict__ in,
                                                            float* __restrict__ P, int32_t nchan,
@@ -381,7 +379,7 @@ __global__ __launch_bounds__(256) void detect_tiled_kernel(const void* __restric
 }
 
 bool detect_tiled_fits(const BeamPlan& p) {
-  if (p.nchan < 2 || p.n_int > kDetectTiledMax) return false;
+  if (!detect_from_record(p.dtype == CDD_CF32, p.nchan, p.nsamp, p.n_int)) return false;
   return ((int64_t)(p.nchan + 63) / 64) * ((p.t_int + 31) / 32) <= 0x7fffffffLL;
 }
 

@@ -37,4 +37,35 @@ inline bool two_blocks_pay(int N, double trials, int64_t blocks, int64_t doubled
   return (double)doubled <= limit * (double)blocks * (1.0 + 1e-12);
 }
 
+// Whether the incoherent path detects straight from the time-major record or from
+// a channel-major copy.  A thread of the direct form adds up the n_int samples of
+// its 4 outputs (8 where it has one channel) in turn, a serial chain that lasts as
+// long for a small record as for a large one; the copy costs its bytes and two
+// launches.  A call on new inputs (us), copy -> direct:
+//                        n_int 16     24            32            64
+//   8 bits  16 x 4,000   19 -> 14     19 -> 20      19 -> 25      19 -> 42
+//           16 x 40,000  19 -> 16     19 -> 21      19 -> 27      23 -> 47
+//           64 x 40,000  24 -> 16     22 -> 21      26 -> 25      28 -> 46
+//           2 x 400,000  25 -> 18     25 -> 20      26 -> 20      31 -> 40
+//          16 x 400,000  64 -> 19     62 -> 25      66 -> 30      75 -> 54
+//   float   16 x 4,000   19 -> 15     19 -> 21      19 -> 26      19 -> 47
+//           64 x 40,000  35 -> 24     33 -> 31      32 -> 39      32 -> 68
+//           2 x 400,000  47 -> 21     53 -> 27      54 -> 29      59 -> 50
+//          512 x 40,000 346 -> 39    399 -> 43     359 -> 52     370 -> 79
+//          128 x 4,000   20 -> 23     20 -> 31      21 -> 35      24 -> 68
+// With fewer than 32 outputs the chain is shorter (500 samples, n_int 48: 19 -> 16).
+inline bool detect_from_record(bool float_samples, int64_t nchan, int64_t nsamp, int n_int) {
+  if (nchan < 2 || n_int > 64) return false;
+  // the chain, against the time of the copy's launches
+  const int64_t rounds = std::min<int64_t>(4, (nsamp / n_int + 7) / 8);
+  const int64_t chain = rounds < 4      ? 96
+                        : float_samples ? (nchan <= 4 ? 72 : nchan < 100 ? 64 : 48)
+                                        : (nchan <= 256 ? 80 : 64);
+  if (n_int * rounds <= chain) return true;
+  // else the record must be large enough for the copy's bytes to outlast the chain
+  const int64_t samples = nchan * nsamp;
+  if (n_int > 32) return samples >= 6000000 || (float_samples && nsamp >= 200000);
+  return samples >= (n_int <= 20 ? 1500000 : 3000000) || nsamp >= 200000;
+}
+
 }  // namespace cdd

@@ -40,8 +40,30 @@ static void test_two_blocks() {
   }
 }
 
+// Detection straight from the record: the sizes measured on both sides of the line.
+static void test_detection() {
+  for (int f = 0; f < 2; ++f) {
+    CHECK(!detect_from_record(f, 1, 1 << 20, 4) && !detect_from_record(f, 512, 1 << 20, 65));
+    for (int n_int = 1; n_int <= 16; ++n_int)
+      CHECK(detect_from_record(f, 2, 16, n_int) && detect_from_record(f, 64, 4000, n_int) &&
+            detect_from_record(f, 4096, 100000, n_int));
+    for (int64_t c : {2, 4, 16, 32, 64})
+      for (int64_t t : {4000, 40000})
+        for (int n_int : {25, 32, 48, 64}) CHECK(!detect_from_record(f, c, t, n_int));
+    for (int n_int : {17, 24, 32, 48, 64}) {
+      CHECK(detect_from_record(f, 512, 40000, n_int) && detect_from_record(f, 16, 400000, n_int));
+      CHECK(detect_from_record(f, 2, 400000, n_int) == (f || n_int <= 32));
+    }
+    CHECK(detect_from_record(f, 2, 500, 48) && detect_from_record(f, 512, 500, 64));
+  }
+  CHECK(detect_from_record(false, 16, 4000, 20) && !detect_from_record(true, 16, 4000, 20));
+  CHECK(detect_from_record(false, 128, 4000, 16) && !detect_from_record(true, 128, 4000, 16));
+  CHECK(detect_from_record(true, 128, 4000, 12) && detect_from_record(true, 512, 4000, 16));
+}
+
 int main() {
   test_two_blocks();
+  test_detection();
   if (g_fail) {
     std::printf("%d failures\n", g_fail);
     return 1;
