@@ -68,4 +68,18 @@ inline bool detect_from_record(bool float_samples, int64_t nchan, int64_t nsamp,
   return samples >= (n_int <= 20 ? 1500000 : 3000000) || nsamp >= 200000;
 }
 
+// Threads per phase bin of a fold (each takes every so many-th period): a workgroup
+// while the bins do not fill the card by themselves, then a wave; a thread with more
+// bins than resident waves, or with a few periods only, which leave a wave's lanes
+// idle.  1,000,000 samples (us), thread -> wave:
+//   periods      1           2           3           4
+//   1025 bins  248 -> 353  226 -> 179  220 -> 121  222 -> 90
+//   4096 bins   56 -> 123   56 -> 62    56 -> 42    58 -> 32
+//   8192 bins   30 -> 99    30 -> 51    30 -> 36    31 -> 28
+inline int fold_threads(int64_t t_int, double period, int nbins) {
+  if (nbins <= 1024) return 256;
+  const int least = 2 + (nbins > 2048) + (nbins > 4096);
+  return nbins <= 8192 && (double)t_int >= least * period ? 64 : 1;
+}
+
 }  // namespace cdd

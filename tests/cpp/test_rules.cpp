@@ -61,8 +61,18 @@ static void test_detection() {
   CHECK(detect_from_record(true, 128, 4000, 12) && detect_from_record(true, 512, 4000, 16));
 }
 
+static void test_fold() {
+  CHECK(fold_threads(1000, 1000.0, 1) == 256 && fold_threads(1000, 1.5, 1024) == 256);
+  CHECK(fold_threads(1000, 500.0, 1025) == 64 && fold_threads(1000, 501.0, 1025) == 1);
+  CHECK(fold_threads(999, 333.0, 4096) == 64 && fold_threads(999, 334.0, 4096) == 1);
+  CHECK(fold_threads(1000, 250.0, 8192) == 64 && fold_threads(1000, 251.0, 8192) == 1);
+  CHECK(fold_threads(1000000, 1.5, 8192) == 64 && fold_threads(1000, 1e6, 8192) == 1);
+  CHECK(fold_threads(1000, 1.5, 8193) == 1);
+}
+
 int main() {
   test_two_blocks();
+  test_fold();
   test_detection();
   if (g_fail) {
     std::printf("%d failures\n", g_fail);
