@@ -963,12 +963,13 @@ static int resident_workgroups(const void* fn, int threads, int64_t* out) {
 }
 
 // What schedule S needs in the arguments: its twiddles, its gain correction and,
-// for a first pass on the matrix cores, their fragments.
+// for a first pass on the matrix cores, their fragments.  The fragments come with
+// the twiddles whatever the sample type, so that one call at a length, of any type,
+// has uploaded all that later calls at it need (they may be under stream capture).
 template <class S>
 static int tables_of(BlockArgs& a) {
-  const bool matrix = mf_schedule<S>() && a.dtype == CDD_CI8;
-  a.gain = matrix ? gain_of<S, true>() : gain_of<S>();
-  if (matrix) {
+  a.gain = mf_schedule<S>() && a.dtype == CDD_CI8 ? gain_of<S, true>() : gain_of<S>();
+  if constexpr (mf_schedule<S>()) {
     const int err = cached_table("mfma32", &make_mf_table, &a.mf);
     if (err) return err;
   }
