@@ -555,6 +555,7 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
       const void* h = nullptr;
     };
     std::vector<Launch> launches;
+    std::vector<int> table_variant(nb, 0);  // the schedule that reads each beam's chirp table
     std::vector<char> staged(plan->host_tab_bytes, 0);
     // beams in the order their inputs are ready: shortest layout change first
     std::vector<size_t> order(nb);
@@ -583,6 +584,7 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
             L.direct = true;
             L.bb = bb;
             L.h = h;
+            table_variant[b] = plan->beams[b].variant;
           } else if ((e = prepare_launch(kLaunchBatch, &bb, &h, 1, staged.data() + L.slot,
                                          &L.d))) {
             return device_fail("launch table", e);
@@ -617,6 +619,7 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
         const int k = kind * 2 + (p.dtype == CDD_CI8 ? 0 : 1);
         group[k].push_back(bb);
         gh[k].push_back(H[b]);
+        if (H[b]) table_variant[b] = launch_variant(kind, p.N, p.variant);
       }
       for (int k = 0; k < kGroupKinds; ++k) {
         if (group[k].empty()) continue;
@@ -662,8 +665,6 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
     // later beams beside the transforms of earlier ones slows both down on
     // this GPU as much as it hides); the single-launch form changes every
     // layout first.
-    // (the single-launch form runs the default schedule of each length)
-    auto variant_of = [&](size_t b) { return plan->single_launch ? 0 : plan->beams[b].variant; };
     auto fused = [&](size_t b) { return H[b] && transpose_chirp_fits(plan->beams[b]); };
     auto d_of = [&](size_t b) { return (int32_t*)(ws + plan->ws_base[b] + plan->lay[b].d_off); };
     bool use_aux = false;
@@ -683,7 +684,7 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
       int err = 0;
       void* tok = nullptr;
       if ((err = stage_begin(kStageDelays, aux.aux, &tok)) ||
-          (H[b] && (err = launch_chirp_table(p, p.dms[0], H[b], aux.aux, variant_of(b)))) ||
+          (H[b] && (err = launch_chirp_table(p, p.dms[0], H[b], aux.aux, table_variant[b]))) ||
           (err = launch_delays(p, t0, d_of(b), aux.aux)) ||
           (err = stage_end(kStageDelays, aux.aux, tok)))
         st = device_fail("chirp table or delay launch", err);
@@ -695,7 +696,7 @@ cdd_status cdd_plan_execute(cdd_plan* plan, void* workspace, size_t ws_bytes, vo
       if (p.nchan > 1 &&
           (err = launch_transposed(p, plan->desc[b].voltages, (void*)xt[b], stream,
                                    fused(b) ? H[b] : nullptr, p.dms[0],
-                                   fused(b) ? d_of(b) : nullptr, variant_of(b)))) {
+                                   fused(b) ? d_of(b) : nullptr, table_variant[b]))) {
         st = device_fail("transpose launch", err);
         break;
       }

@@ -737,8 +737,6 @@ constexpr int kMixLds =
          cmax(mix_lds_floats<MixSched<4096>>(), mix_lds_floats<MixSched<8192>>()));
 constexpr bool mix_len_ok(int lg) { return lg >= 8 && lg <= 13; }
 static_assert(MixSched<8192>::T == kMixT && MixSched<256>::T <= kMixT, "mixed schedules");
-// (chirp tables are laid out for the default schedules: the same last radix)
-static_assert(MixSched<4096>::rad_f(2) == SchedFor<4096, 0>::type::rad_f(2), "table layout");
 
 template <class S, int DT, bool MULTI>
 __device__ __forceinline__ void mix_unit(const BlockArgs& a, int64_t unit, float* lds) {
@@ -1149,6 +1147,19 @@ bool batch_variant_ok(int N, int V) {
 }
 
 bool mixed_supported(int N) { return N >= 256 && N <= 8192 && (N & (N - 1)) == 0; }
+
+// The schedule a launch kind runs for length N and variant V.
+int launch_variant(int kind, int N, int V) {
+  if (kind == kLaunchMixed) return N == 4096 ? 3 : 0;
+  return kind == kLaunchBatch ? V : 0;
+}
+static_assert(std::is_same_v<MixSched<256>, SchedFor<256, 0>::type> &&
+                  std::is_same_v<MixSched<512>, SchedFor<512, 0>::type> &&
+                  std::is_same_v<MixSched<1024>, SchedFor<1024, 0>::type> &&
+                  std::is_same_v<MixSched<2048>, SchedFor<2048, 0>::type> &&
+                  std::is_same_v<MixSched<4096>, SchedFor<4096, 3>::type> &&
+                  std::is_same_v<MixSched<8192>, SchedFor<8192, 0>::type>,
+              "launch_variant names the mixed kernel's schedules");
 
 // Calls f with the schedule a launch kind runs for (N, V).
 template <class F>

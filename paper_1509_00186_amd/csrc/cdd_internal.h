@@ -102,7 +102,7 @@ int launch_block_co(const BeamPlan& p, const Coords& co, const void* xt, const D
                     float* P, void* vout, const void* H, void* stream);
 size_t chirp_table_bytes(const BeamPlan& p);
 // (laid out for schedule `variant` of the length, which the kernel that reads
-// it must run: p.variant, or 0 for the launches that run the default schedule)
+// it must run: p.variant, or that of launch_variant)
 int launch_chirp_table(const BeamPlan& p, double dm, void* H, void* stream, int variant);
 // The layout change of a whole record (into [c][xt_stride]) with the
 // one-DM chirp table (and, if delays is set, the channel delays at that DM)
@@ -162,6 +162,9 @@ struct LaunchDesc {
   int64_t total = 0;  // work units
   double unit_points = 0;  // points transformed per unit of work (mean), all trials
 };
+// The schedule (variant of its length) that a launch runs, and so reads a chirp
+// table of; V is the beam's own.
+int launch_variant(int kind, int N, int V);
 bool mixed_supported(int N);
 bool batch_variant_ok(int N, int V);  // schedules the persistent batch kernel has
 // Form the per-beam argument table of one launch in host_tab

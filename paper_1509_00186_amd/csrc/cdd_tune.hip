@@ -188,7 +188,7 @@ extern "C" cdd_status cdd_autotune(int32_t dtype, int32_t nchan, double f_centre
             // then the launch (the host table is the same every time)
             auto run = [&]() -> int {
               int r = 0;
-              if (H) r = launch_chirp_table(p, bb.dms.dm[0], H, st, 0);
+              if (H) r = launch_chirp_table(p, bb.dms.dm[0], H, st, launch_variant(d.kind, N, v));
               return r ? r : enqueue_launch(d, host_tab.data(), tab, counter, st);
             };
             if (!err) err = run();  // warm-up (and the twiddle tables)
