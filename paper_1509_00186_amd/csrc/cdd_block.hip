@@ -91,7 +91,8 @@ struct BlockArgs {
   int32_t nchan, M, nfront, n_int, dtype, phase_mode, exact_div, taper;
   int32_t accum;        // add to P instead of storing (second polarisation)
   int32_t lgn;          // log2 N (mixed launches switch on it)
-  float gain;           // DM tiles: relative correction of the transforms' gain (gain_of)
+  float gain;           // DM tiles, even spacing: relative correction of the gain (gain_of)
+  ScaleFactors scale;   // DM tiles, other spacing: 1/N with the correction
   double f_lo, df, dconst;
   double dm_step;       // DM tiles: dms.dm[i] = dms.dm[0] + i dm_step, or 0 if not so spaced
   DmTile dms;
@@ -528,13 +529,13 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
     // The taper depends on the bin only: it scales the shared spectrum once,
     // and the per-trial chirp is a pure rotation.
     if (a.taper) apply_taper<S>(v, a.taper, t);
-    // the inverse transform's 1/N (a power of two, so exact) once per item
+    // the inverse transform's 1/N and the gain correction once per item (stepped:
+    // 1/N alone, a power of two, and the first rotation carries the correction)
     constexpr float inv_n = 1.0f / (float)S::N;
     float2 X[S::E];
-    const float gx = stepped ? 0.0f : a.gain;  // (the first rotation carries it)
+    const float sa = stepped ? inv_n : a.scale.a, sb = stepped ? 1.0f : a.scale.b;
 #pragma unroll
-    for (int e = 0; e < S::E; ++e)
-      X[e] = make_float2(fmaf(v[e].x, gx, v[e].x) * inv_n, fmaf(v[e].y, gx, v[e].y) * inv_n);
+    for (int e = 0; e < S::E; ++e) X[e] = make_float2(v[e].x * sa * sb, v[e].y * sa * sb);
     const bool per_dm = qd != nullptr && a.phase_mode == CDD_PHASE_FP64_REDUCED;
     if (stepped) {
       // X becomes the chirped spectrum of the current trial; the table then
@@ -960,13 +961,26 @@ static int resident_workgroups(const void* fn, int threads, int64_t* out) {
   return 0;
 }
 
+// 1/N with the gain correction of schedule S (HW: and of the hardware's rotation,
+// which forms the chirp of DM tiles that are not evenly spaced).
+template <class S, bool EXACT_FIRST, bool HW>
+static ScaleFactors tile_scale() {
+  static const ScaleFactors f = scale_factors(
+      (1.0 + (double)gain_of<S, EXACT_FIRST>() - (HW ? kHwRotationGain : 0.0)) / (double)S::N);
+  return f;
+}
+
 // What schedule S needs in the arguments: its twiddles, its gain correction and,
 // for a first pass on the matrix cores, their fragments.  The fragments come with
 // the twiddles whatever the sample type, so that one call at a length, of any type,
 // has uploaded all that later calls at it need (they may be under stream capture).
 template <class S>
 static int tables_of(BlockArgs& a) {
-  a.gain = mf_schedule<S>() && a.dtype == CDD_CI8 ? gain_of<S, true>() : gain_of<S>();
+  const bool matrix = mf_schedule<S>() && a.dtype == CDD_CI8;
+  a.gain = matrix ? gain_of<S, true>() : gain_of<S>();
+  a.scale = a.phase_mode == CDD_PHASE_FP64_REDUCED
+                ? (matrix ? tile_scale<S, true, true>() : tile_scale<S, false, true>())
+                : (matrix ? tile_scale<S, true, false>() : tile_scale<S, false, false>());
   if constexpr (mf_schedule<S>()) {
     const int err = cached_table("mfma32", &make_mf_table, &a.mf);
     if (err) return err;

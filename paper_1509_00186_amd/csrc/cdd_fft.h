@@ -520,12 +520,15 @@ __device__ __forceinline__ float2 expi_neg_turns_fp64(double x, double scale) {
   return make_float2((float)(scale * c), (float)(-scale * sn));
 }
 
-// exp(-2 pi i x) for |x| <= 1/2 turn to within an FP32 rounding or two: the
-// quadrant n = rint(4x) taken out exactly in FP64, then the Taylor series of
+// (1 + gain) exp(-2 pi i x) for |x| <= 1/2 turn to within an FP32 rounding or two:
+// the quadrant n = rint(4x) taken out exactly in FP64, then the Taylor series of
 // sine and cosine on [-pi/4, pi/4] in FP32 through the 9th and 10th powers
 // (truncation below 2e-9).  About 20 FP32 operations; the hardware sine and
 // cosine have an absolute error of 1.2e-7, more than the transforms around them.
-__device__ __forceinline__ float2 expi_neg_turns_fp32(double x) {
+// The gain (of the order of the rounding) is added to the small terms, before the
+// rounding of the whole: applied to the rounded sine and cosine it would move some
+// of them by a whole unit and most not at all.
+__device__ __forceinline__ float2 expi_neg_turns_fp32(double x, float gain) {
   const double n = rint(4.0 * x);
   const float d = (float)fma(n, -0.25, x);
   const float th = fmaf(d, 6.2831855f, d * -1.7484556e-07f);  // 2 pi in two parts
@@ -533,12 +536,12 @@ __device__ __forceinline__ float2 expi_neg_turns_fp32(double x) {
   float sp = fmaf(t2, 2.7557319e-06f, -1.9841270e-04f);
   sp = fmaf(t2, sp, 8.3333333e-03f);
   sp = fmaf(t2, sp, -1.6666667e-01f);
-  const float sv = fmaf(th * t2, sp, th);
+  const float sv = fmaf(th, fmaf(t2, sp, gain), th);
   float cp = fmaf(t2, -2.7557319e-07f, 2.4801587e-05f);
   cp = fmaf(t2, cp, -1.3888889e-03f);
   cp = fmaf(t2, cp, 4.1666667e-02f);
   cp = fmaf(t2, cp, -0.5f);
-  const float cv = fmaf(t2, cp, 1.0f);
+  const float cv = 1.0f + fmaf(t2, cp, fmaf(t2, -0.5f * gain, gain));  // gain cos(th)
   const int q = (int)n & 3;  // exp(2 pi i x) = i^q exp(i th)
   const float c = q & 1 ? sv : cv, sn = q & 1 ? cv : sv;
   return make_float2((q == 1 || q == 2) ? -c : c, q >= 2 ? sn : -sn);
@@ -597,9 +600,9 @@ __device__ __forceinline__ void chirp_table_part(const ChirpTableArgs& a, unsign
       const double sd = (double)s;
       const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                  : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
-      const float2 h = expi_neg_turns_fp32(q - rint(q));
+      const float2 h = expi_neg_turns_fp32(q - rint(q), a.gain);
       const float gn = taper_gain<false>(taper, (float)s * inv_n) * inv_n;
-      row[e] = make_float2(fmaf(h.x, a.gain, h.x) * gn, fmaf(h.y, a.gain, h.y) * gn);
+      row[e] = make_float2(h.x * gn, h.y * gn);
     }
   } else {
     const float fcf = (float)fc;
@@ -650,7 +653,7 @@ std::vector<float2> make_twiddles() {
 // the largest error of summed intensities, in which random rounding averages
 // out (512 channels: 2.5e-7 relative, 7e-8 without it).  The chirp takes the
 // loss out again, as a relative correction applied before its entries are
-// rounded.
+// rounded (in DM tiles: scale_factors).
 // Power gain of the constants of an in-register DFT of R points:
 inline double dft_const_gain(int R) {
   if (R <= 4) return 1.0;
@@ -700,6 +703,29 @@ double gain_correction(bool exact_first = false) {
   }
   return -0.5 * lg;
 }
+// Mean gain of the hardware's sine and cosine over a turn: the mean of
+// sqrt(cos^2 + sin^2) - 1 over 2^24 phases.
+constexpr double kHwRotationGain = -3.23e-8;
+
+// The factor s, which need not be an FP32 number, as two FP32 factors: their product
+// is within 1e-10 of it.
+struct ScaleFactors {
+  float a, b;
+};
+inline ScaleFactors scale_factors(double s) {
+  ScaleFactors best{1.0f, (float)s};
+  double err = 1.0;
+  for (int i = 1; i < 4096; ++i) {
+    const float a = 1.0f + (float)i * 0x1p-12f, b = (float)(s / (double)a);
+    const double e = std::fabs((double)a * (double)b / s - 1.0);
+    if (e < err) {
+      err = e;
+      best = {a, b};
+    }
+  }
+  return best;
+}
+
 template <class S, bool EXACT_FIRST = false>
 float gain_of() {
   static const float g = (float)gain_correction<S>(EXACT_FIRST);

@@ -281,8 +281,8 @@ __device__ __forceinline__ float2 chan_chirp(const LargeArgs& a, double fc, int6
     const double x = beta * sd;
     const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                  : (B * (sd * sd)) * fma(x, x, 1.0 - x);
-    const float2 h = expi_neg_turns_fp32(q - rint(q));
-    return make_float2(fmaf(h.x, a.gain, h.x) * g, fmaf(h.y, a.gain, h.y) * g);
+    const float2 h = expi_neg_turns_fp32(q - rint(q), a.gain);
+    return make_float2(h.x * g, h.y * g);
   }
   const float fcf = (float)fc;
   const float Af = (float)(a.dconst * a.dm) / (fcf * fcf);
@@ -610,9 +610,9 @@ __device__ __forceinline__ float2 band_chirp(const LargeArgs& a, uint32_t j, flo
   r = fma(r, fma(-den, r, 1.0), r);
   double q = num * r;
   q = fma(r, fma(-den, q, num), q);
-  const float2 h = expi_neg_turns_fp32(q - rint(q));
+  const float2 h = expi_neg_turns_fp32(q - rint(q), a.gain);
   const float g = inv_n * taper_gain<false>(a.taper, (float)j * inv_n - 0.5f);
-  return make_float2(fmaf(h.x, a.gain, h.x) * g, fmaf(h.y, a.gain, h.y) * g);
+  return make_float2(h.x * g, h.y * g);
 }
 
 // The chirp function of one call for every real-spectrum bin, shared by all
@@ -908,10 +908,6 @@ struct Split {
 // real points 0.156 -> 0.144 ms.  (With the real series each workgroup holds
 // mirror-row pairs, so the count stays even.)
 constexpr int rows_per_group(int T) { return T * 8 <= 256 ? 8 : 256 / T; }
-
-// Mean gain of the hardware's sine and cosine over a turn (measured: the mean of
-// sqrt(cos^2 + sin^2) - 1 over 2^24 phases).
-constexpr double kHwRotationGain = -3.23e-8;
 
 // Relative gain correction of a whole transform pair (see gain_correction): its
 // sub-transforms, and one hardware rotation each way per level above the first.
