@@ -91,8 +91,8 @@ struct BlockArgs {
   int32_t nchan, M, nfront, n_int, dtype, phase_mode, exact_div, taper;
   int32_t accum;        // add to P instead of storing (second polarisation)
   int32_t lgn;          // log2 N (mixed launches switch on it)
-  float gain;           // DM tiles, even spacing: relative correction of the gain (gain_of)
-  ScaleFactors scale;   // DM tiles, other spacing: 1/N with the correction
+  double first;         // DM tiles, even spacing: size of the first rotation (tile_size)
+  ScaleFactors scale;   // DM tiles, other spacing: the same as factors of the spectrum
   double f_lo, df, dconst;
   double dm_step;       // DM tiles: dms.dm[i] = dms.dm[0] + i dm_step, or 0 if not so spaced
   DmTile dms;
@@ -227,10 +227,9 @@ __device__ __forceinline__ void apply_chirp_dm(float2* v, double dm, const doubl
 // 512-channel beam, the intensities of 64 trials differ from 64 one-DM calls
 // by 1.1e-7 relative L2).  Entries as in chirp_phase_per_dm (whose LDS the
 // table takes).
-// rs[] receives (1 + gain) exp(-2 pi i DM Q) of this thread's bins for the
-// given DM.
+// rs[] receives size exp(-2 pi i DM Q) of this thread's bins for the given DM.
 template <class S>
-__device__ __forceinline__ void rotation_table(float2* rs, double dm, float gain, double fc,
+__device__ __forceinline__ void rotation_table(float2* rs, double dm, double size, double fc,
                                                const BlockArgs& a, int t, int g, int ng) {
   constexpr int N = S::N;
   const double dfn = a.df / (double)N;
@@ -242,7 +241,7 @@ __device__ __forceinline__ void rotation_table(float2* rs, double dm, float gain
     const double sd = bin_offset<S>(e, t);
     const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                  : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
-    rs[e * S::T + t] = expi_neg_turns_fp64(q - rint(q), 1.0 + (double)gain);
+    rs[e * S::T + t] = expi_neg_turns_fp64(q - rint(q), size);
   }
 }
 
@@ -267,6 +266,12 @@ __device__ __forceinline__ void apply_taper(float2* v, int kind, int t) {
       v[b * R + r] = make_float2(v[b * R + r].x * w, v[b * R + r].y * w);
     }
   }
+}
+
+// Factor that the forward transform of schedule S carries.
+template <class S>
+constexpr float first_scale(int dtype) {
+  return mf_schedule<S>() && dtype == CDD_CI8 ? kMfScale : 1.0f;
 }
 
 // Single DM: multiply by the channel's chirp row (its layout: see
@@ -507,7 +512,7 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
   const bool stepped = MULTI && qd != nullptr && a.phase_mode == CDD_PHASE_FP64_REDUCED &&
                        a.dm_step != 0.0;
   if (stepped) 
-    rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], a.gain, fc, a, t, g, ng);
+    rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], a.first, fc, a, t, g, ng);
   float2 v[S::E];
   if constexpr (DT == CDD_CI8 && mf_schedule<S>()) {
     unsigned w[S::E];
@@ -529,11 +534,10 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
     // The taper depends on the bin only: it scales the shared spectrum once,
     // and the per-trial chirp is a pure rotation.
     if (a.taper) apply_taper<S>(v, a.taper, t);
-    // the inverse transform's 1/N and the gain correction once per item (stepped:
-    // 1/N alone, a power of two, and the first rotation carries the correction)
-    constexpr float inv_n = 1.0f / (float)S::N;
+    // the inverse transform's 1/N, the gain correction and the scale of the first pass
+    // once per item (stepped: in the first rotation)
     float2 X[S::E];
-    const float sa = stepped ? inv_n : a.scale.a, sb = stepped ? 1.0f : a.scale.b;
+    const float sa = stepped ? 1.0f : a.scale.a, sb = stepped ? 1.0f : a.scale.b;
 #pragma unroll
     for (int e = 0; e < S::E; ++e) X[e] = make_float2(v[e].x * sa * sb, v[e].y * sa * sb);
     const bool per_dm = qd != nullptr && a.phase_mode == CDD_PHASE_FP64_REDUCED;
@@ -543,7 +547,7 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
       float2* rs = reinterpret_cast<float2*>(qd);
       step_chirp<S>(X, rs, t);
       if (ng > 1) __syncthreads();  // every group has read the table
-      rotation_table<S>(rs, a.dm_step, 0.0f, fc, a, t, g, ng);
+      rotation_table<S>(rs, a.dm_step, 1.0, fc, a, t, g, ng);
       for (int i = 0; i < a.dms.ndm; ++i) {
         int tt = t;
         asm volatile("" : "+v"(tt));
@@ -961,12 +965,18 @@ static int resident_workgroups(const void* fn, int threads, int64_t* out) {
   return 0;
 }
 
-// 1/N with the gain correction of schedule S (HW: and of the hardware's rotation,
-// which forms the chirp of DM tiles that are not evenly spaced).
-template <class S, bool EXACT_FIRST, bool HW>
-static ScaleFactors tile_scale() {
-  static const ScaleFactors f = scale_factors(
-      (1.0 + (double)gain_of<S, EXACT_FIRST>() - (HW ? kHwRotationGain : 0.0)) / (double)S::N);
+// What the chirp of DM tiles multiplies by besides its rotation: 1/N, the gain
+// correction of schedule S and the inverse of its first pass's scale.
+template <class S, bool MATRIX>
+static double tile_size() {
+  return (1.0 + (double)gain_of<S, MATRIX>()) / ((double)S::N * (MATRIX ? kMfScale : 1.0f));
+}
+// ... as factors of the spectrum (HW: with the loss of the hardware's rotation, which
+// forms the chirp of tiles that are not evenly spaced).
+template <class S, bool MATRIX, bool HW>
+static ScaleFactors tile_factors() {
+  static const ScaleFactors f =
+      scale_factors(tile_size<S, MATRIX>() * (1.0 - (HW ? kHwRotationGain : 0.0)));
   return f;
 }
 
@@ -977,10 +987,10 @@ static ScaleFactors tile_scale() {
 template <class S>
 static int tables_of(BlockArgs& a) {
   const bool matrix = mf_schedule<S>() && a.dtype == CDD_CI8;
-  a.gain = matrix ? gain_of<S, true>() : gain_of<S>();
+  a.first = matrix ? tile_size<S, true>() : tile_size<S, false>();
   a.scale = a.phase_mode == CDD_PHASE_FP64_REDUCED
-                ? (matrix ? tile_scale<S, true, true>() : tile_scale<S, false, true>())
-                : (matrix ? tile_scale<S, true, false>() : tile_scale<S, false, false>());
+                ? (matrix ? tile_factors<S, true, true>() : tile_factors<S, false, true>())
+                : (matrix ? tile_factors<S, true, false>() : tile_factors<S, false, false>());
   if constexpr (mf_schedule<S>()) {
     const int err = cached_table("mfma32", &make_mf_table, &a.mf);
     if (err) return err;
@@ -1079,16 +1089,17 @@ size_t chirp_table_bytes(const BeamPlan& p) {
 }
 
 // What the one-DM chirp table depends on in schedule V of length N: the radix
-// of the last forward pass (its order) and the gain correction.
+// of the last forward pass (its order), and the size of its entries: the gain
+// correction and the inverse of the first pass's scale.
 struct TableForm {
   int radix;
-  float gain;
+  double size;
 };
 template <int N, int V>
 static TableForm table_form(int dtype) {
   using S = typename SchedFor<N, V>::type;
-  return {S::rad_f(S::NP - 1),
-          mf_schedule<S>() && dtype == CDD_CI8 ? gain_of<S, true>() : gain_of<S>()};
+  const float gain = mf_schedule<S>() && dtype == CDD_CI8 ? gain_of<S, true>() : gain_of<S>();
+  return {S::rad_f(S::NP - 1), (1.0 + (double)gain) / (double)first_scale<S>(dtype)};
 }
 static TableForm table_form_of(int N, int v, int dtype) {
   switch (N) {
@@ -1120,7 +1131,7 @@ ChirpTableArgs chirp_table_args(const BeamPlan& p, double dm, void* H, int kpt, 
   ChirpTableArgs a{};
   const TableForm f = table_form_of(p.N, variant, p.dtype);
   a.lgJ = log2i(p.N / f.radix);
-  a.gain = f.gain;
+  a.size = rotation_size(f.size);
   a.H = (float2*)H;
   a.f_lo = p.f_lo;
   a.df = p.df;

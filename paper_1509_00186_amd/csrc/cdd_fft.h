@@ -520,15 +520,29 @@ __device__ __forceinline__ float2 expi_neg_turns_fp64(double x, double scale) {
   return make_float2((float)(scale * c), (float)(-scale * sn));
 }
 
-// (1 + gain) exp(-2 pi i x) for |x| <= 1/2 turn to within an FP32 rounding or two:
-// the quadrant n = rint(4x) taken out exactly in FP64, then the Taylor series of
+// Size of a rotation: k (1 + gain), gain of the order of the rounding, with 2 pi k as
+// the sum of two FP32 numbers.
+struct RotationSize {
+  float k = 1.0f, gain = 0.0f, hi = 6.2831855f, lo = -1.7484556e-07f;
+};
+inline RotationSize rotation_size(double size) {
+  RotationSize r;
+  r.k = (float)size;
+  r.gain = (float)(size / (double)r.k - 1.0);
+  r.hi = (float)(6.283185307179586 * (double)r.k);
+  r.lo = (float)(6.283185307179586 * (double)r.k - (double)r.hi);
+  return r;
+}
+
+// exp(-2 pi i x), of the given size, for |x| <= 1/2 turn to within an FP32 rounding or
+// two: the quadrant n = rint(4x) taken out exactly in FP64, then the Taylor series of
 // sine and cosine on [-pi/4, pi/4] in FP32 through the 9th and 10th powers
 // (truncation below 2e-9).  About 20 FP32 operations; the hardware sine and
 // cosine have an absolute error of 1.2e-7, more than the transforms around them.
-// The gain (of the order of the rounding) is added to the small terms, before the
-// rounding of the whole: applied to the rounded sine and cosine it would move some
+// The size enters the small terms and the factors of the last operation, before the
+// rounding of the whole: applied to the rounded sine and cosine, a gain would move some
 // of them by a whole unit and most not at all.
-__device__ __forceinline__ float2 expi_neg_turns_fp32(double x, float gain) {
+__device__ __forceinline__ float2 expi_neg_turns_fp32(double x, const RotationSize& z) {
   const double n = rint(4.0 * x);
   const float d = (float)fma(n, -0.25, x);
   const float th = fmaf(d, 6.2831855f, d * -1.7484556e-07f);  // 2 pi in two parts
@@ -536,12 +550,14 @@ __device__ __forceinline__ float2 expi_neg_turns_fp32(double x, float gain) {
   float sp = fmaf(t2, 2.7557319e-06f, -1.9841270e-04f);
   sp = fmaf(t2, sp, 8.3333333e-03f);
   sp = fmaf(t2, sp, -1.6666667e-01f);
-  const float sv = fmaf(th, fmaf(t2, sp, gain), th);
+  const float kth = fmaf(d, z.hi, d * z.lo);
+  const float sv = fmaf(kth, fmaf(t2, sp, z.gain), kth);
   float cp = fmaf(t2, -2.7557319e-07f, 2.4801587e-05f);
   cp = fmaf(t2, cp, -1.3888889e-03f);
   cp = fmaf(t2, cp, 4.1666667e-02f);
   cp = fmaf(t2, cp, -0.5f);
-  const float cv = 1.0f + fmaf(t2, cp, fmaf(t2, -0.5f * gain, gain));  // gain cos(th)
+  const float g = fmaf(t2, -0.5f * z.gain, z.gain);  // gain cos(th)
+  const float cv = fmaf(z.k, fmaf(t2, cp, g), z.k);
   const int q = (int)n & 3;  // exp(2 pi i x) = i^q exp(i th)
   const float c = q & 1 ? sv : cv, sn = q & 1 ? cv : sv;
   return make_float2((q == 1 || q == 2) ? -c : c, q >= 2 ? sn : -sn);
@@ -557,7 +573,8 @@ __device__ __forceinline__ float2 expi_neg_turns_fp32(double x, float gain) {
 // constants are formed once per thread for kpt entries of one channel.  The
 // reduction r = q - rint(q) to [-1/2, 1/2] turns is FP64; sin/cos of 2 pi r
 // are FP32.  The FP32 phase mode forms q itself in FP32 (precision study).
-// The taper (Sec. 2.2) scales the entry with the 1/N of the inverse transform.
+// The taper (Sec. 2.2) scales the entry with the 1/N of the inverse transform; a.size
+// takes out a factor that the forward transform carries (first_scale).
 // Order of a row: the block kernel's threads hold bins j + r N/R (R the radix
 // of its last forward pass, r < R); the bins of even r and of r + 1 lie side by
 // side at 2 (r/2 N/R + j), so that one 16-byte load gives a lane two of them.
@@ -565,7 +582,7 @@ struct ChirpTableArgs {
   float2* H;
   double f_lo, df, dconst, dm;
   int32_t lgN, lgJ, kpt, phase_mode, taper, exact_div;  // lgJ = log2(N/R)
-  float gain;    // relative correction of the transforms' gain (gain_of)
+  RotationSize size;  // correction of the transforms' gain, and their scale taken out
   uint32_t nwg;  // workgroups of 256 threads covering the table (nchan N / (256 kpt))
 };
 
@@ -600,7 +617,7 @@ __device__ __forceinline__ void chirp_table_part(const ChirpTableArgs& a, unsign
       const double sd = (double)s;
       const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                  : (sd * sd) * fma(sd, fma(sd, Bbb, -Bb), B);
-      const float2 h = expi_neg_turns_fp32(q - rint(q), a.gain);
+      const float2 h = expi_neg_turns_fp32(q - rint(q), a.size);
       const float gn = taper_gain<false>(taper, (float)s * inv_n) * inv_n;
       row[e] = make_float2(h.x * gn, h.y * gn);
     }
@@ -615,8 +632,8 @@ __device__ __forceinline__ void chirp_table_part(const ChirpTableArgs& a, unsign
       const float q = Af * (f * f) / (fcf + f);
       float sn, cs;
       sincospif(2.0f * q, &sn, &cs);
-      const float gn = taper_gain<false>(taper, (float)s * inv_n) * inv_n;
-      row[e] = make_float2(fmaf(cs, a.gain, cs) * gn, -fmaf(sn, a.gain, sn) * gn);
+      const float gn = taper_gain<false>(taper, (float)s * inv_n) * inv_n * a.size.k;
+      row[e] = make_float2(fmaf(cs, a.size.gain, cs) * gn, -fmaf(sn, a.size.gain, sn) * gn);
     }
   }
 }

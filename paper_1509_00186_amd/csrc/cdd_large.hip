@@ -281,7 +281,7 @@ __device__ __forceinline__ float2 chan_chirp(const LargeArgs& a, double fc, int6
     const double x = beta * sd;
     const double q = a.exact_div ? (B * (sd * sd)) / fma(beta, sd, 1.0)
                                  : (B * (sd * sd)) * fma(x, x, 1.0 - x);
-    const float2 h = expi_neg_turns_fp32(q - rint(q), a.gain);
+    const float2 h = expi_neg_turns_fp32(q - rint(q), RotationSize{1.0f, a.gain});
     return make_float2(h.x * g, h.y * g);
   }
   const float fcf = (float)fc;
@@ -610,7 +610,7 @@ __device__ __forceinline__ float2 band_chirp(const LargeArgs& a, uint32_t j, flo
   r = fma(r, fma(-den, r, 1.0), r);
   double q = num * r;
   q = fma(r, fma(-den, q, num), q);
-  const float2 h = expi_neg_turns_fp32(q - rint(q), a.gain);
+  const float2 h = expi_neg_turns_fp32(q - rint(q), RotationSize{1.0f, a.gain});
   const float g = inv_n * taper_gain<false>(a.taper, (float)j * inv_n - 0.5f);
   return make_float2(h.x * g, h.y * g);
 }

@@ -2,11 +2,14 @@
 //
 // A DFT of 16 complex points is a real 32 x 32 matrix F acting on columns of
 // 32 values (re, im interleaved), so 32 butterflies are one 32 x 32 x 32
-// product: two v_mfma_f32_32x32x16_f16.  8-bit samples are exact in a half, F is
-// carried as a pair of halves, F = Fh + Fl (rounded once from FP64, within
-// 2^-24 of it), and the products accumulate in FP32, so the pass is at least as
-// exact as the FP32 butterflies (their constants are single FP32 numbers).  It
-// takes three vector operations per sample (byte pair to halves) where the
+// product: two v_mfma_f32_32x32x16_f16.  8-bit samples are exact in a half; F is
+// carried as a pair of halves, Fh + Fl, of kMfScale F.  A pair holds 22 bits, two
+// fewer than FP32 for the worst entries (sin(pi/8) would be 2.4e-8 off, 6e-9 as an
+// FP32 number); the scale is one at which all eight magnitudes cos(k pi/16) happen
+// to lie close to pairs: the largest error is 1.4e-9, every entry at or below that of
+// its FP32 number, and none of the parts is a subnormal.  (Three halves without a
+// scale: 512 channels 413 -> 428 us.)  The scale is taken out by the chirp, with the
+// 1/N of the inverse transform.  The products accumulate in FP32.  The pass takes three vector operations per sample (byte pair to halves) where the
 // conversion and the radix-16 butterfly took 14, and the matrix cores, idle
 // otherwise, work beside the vector ALU, which bounds these kernels.  The later
 // passes stay on the vector ALU: their FP32 values would have to be split into
@@ -43,11 +46,13 @@ constexpr bool mf_schedule() {
 // output k(m), k(m) = m with its two middle bits exchanged (so that half h
 // receives k = 8 a + 4 h + b); column 16 s + 8 h + e is component e % 2 of
 // input r = 8 s + 4 h + e / 2.  Kinds: 0 exp(-2 pi i r k/16); 1 (odd inputs of
-// radix 32) exp(-2 pi i k (2r + 1)/32).  Fragment order: kind, s, (hi, lo); 64
-// lanes of 16 bytes each.
+// radix 32) exp(-2 pi i k (2r + 1)/32).  Fragment order: kind, s, part (largest
+// first); 64 lanes of 16 bytes each.
 enum { kMfPlain = 0, kMfOdd = 1, kMfKinds = 2 };
+constexpr int kMfParts = 2;
+constexpr float kMfScale = 4154.09765625f;
 inline std::vector<float2> make_mf_table() {
-  std::vector<float2> out((size_t)kMfKinds * 4 * 64 * 2);  // 16 bytes per lane
+  std::vector<float2> out((size_t)kMfKinds * 2 * kMfParts * 64 * 2);  // 16 bytes per lane
   _Float16* h = (_Float16*)out.data();
   for (int kind = 0; kind < kMfKinds; ++kind)
     for (int s = 0; s < 2; ++s)
@@ -62,26 +67,28 @@ inline std::vector<float2> make_mf_table() {
           // out_re = re x_re - im x_im, out_im = im x_re + re x_im
           const double v = c == ci ? re : c ? im : -im;
           const double z = std::fabs(v) < 1e-9 ? 0.0 : v;
-          const _Float16 hi = (_Float16)z;
-          const _Float16 lo = (_Float16)(z - (double)hi);
-          const size_t f = (size_t)(kind * 2 + s) * 2;
-          h[((f + 0) * 64 + l) * 8 + e] = hi;
-          h[((f + 1) * 64 + l) * 8 + e] = lo;
+          double rest = z * (double)kMfScale;
+          for (int p = 0; p < kMfParts; ++p) {
+            const _Float16 part = (_Float16)rest;
+            rest -= (double)part;
+            h[(((size_t)(kind * 2 + s) * kMfParts + p) * 64 + l) * 8 + e] = part;
+          }
         }
   return out;
 }
 
 struct MfMat {
-  half8v hi[2], lo[2];
+  half8v part[kMfParts][2];
 };
 __device__ __forceinline__ MfMat mf_matrix(const float2* tab, int kind, int lane) {
   MfMat m;
   const auto p = gptr((const uint4v*)tab);
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    m.hi[s] = __builtin_bit_cast(half8v, p[((kind * 2 + s) * 2 + 0) * 64 + lane]);
-    m.lo[s] = __builtin_bit_cast(half8v, p[((kind * 2 + s) * 2 + 1) * 64 + lane]);
-  }
+  for (int i = 0; i < kMfParts; ++i)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      m.part[i][s] =
+          __builtin_bit_cast(half8v, p[((kind * 2 + s) * kMfParts + i) * 64 + lane]);
   return m;
 }
 
@@ -109,13 +116,15 @@ struct MfMap {
   }
 };
 
-// F x for 32 columns of exact halves, small terms first.
+// kMfScale F x for 32 columns of exact halves, small terms first.
 __device__ __forceinline__ float16v mf_mul(const MfMat& F, const half8v* x) {
   float16v acc = {};
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(F.lo[0], x[0], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(F.lo[1], x[1], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(F.hi[0], x[0], acc, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(F.hi[1], x[1], acc, 0, 0, 0);
+#pragma unroll
+  for (int i = kMfParts - 1; i >= 0; --i)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(F.part[i][s], x[s], acc, 0, 0, 0);
+  return acc;
 }
 
 // A sample's two bytes as halves: 0x6400 | u is the half 1024 + u, so
@@ -126,7 +135,7 @@ __device__ __forceinline__ half2v mf_sample(unsigned w) {
   return __builtin_bit_cast(half2v, p) + bias;
 }
 
-// The first pass: w[idx] holds the bytes of this thread's sample idx.
+// The first pass, times kMfScale: w[idx] holds the bytes of this thread's sample idx.
 template <class S, int R>
 __device__ __forceinline__ void mf_first(float2* v, const unsigned* w, const float2* mf, int t) {
   constexpr int PT = R / 2, TILES = S::E / PT;
