@@ -88,6 +88,8 @@ struct BlockArgs {
   int64_t p_stride, p_dm_stride, u_lim;
   int64_t v_stride, o_lim;
   int64_t nblocks, item0;   // blocks per channel; first work item of this beam
+  int64_t units;            // batch kernel: units of work of this beam,
+  int32_t take;             // and how many of them a work item holds
   int32_t nchan, M, nfront, n_int, dtype, phase_mode, exact_div, taper;
   int32_t accum;        // add to P instead of storing (second polarisation)
   int32_t lgn;          // log2 N (mixed launches switch on it)
@@ -658,36 +660,38 @@ __global__ __launch_bounds__(S::T * wave_blocks<S>(),
 // Persistent form for several beams sharing one transform length and sample
 // type (one instantiation per type: a run-time switch between the two load
 // paths makes the register allocator spill): a grid sized to the machine
-// pulls work items (beam, channel, blocks), `take` at a time, from a counter
-// until all are taken; beams are listed longest work first.  Every wave leaves the loop
-// once the counter passes the item count.
+// takes values from a counter, each of which stands for a few units (channel,
+// blocks) of one beam (its `take`; see units_per_value), until all `total` are taken;
+// beams are listed longest work first.  Every wave leaves the loop once the
+// counter passes that number.
 template <class S, int DT, int G>
 __global__ __launch_bounds__(S::T * G, (wg_waves<S, true, G>())) void batch_kernel(
-    const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total, uint32_t take,
+    const BlockArgs* __restrict__ beams, int32_t nbeams, int64_t total,
     unsigned int* __restrict__ counter) {
   __shared__ __align__(16) float lds[G * S::lds_floats()];
   constexpr bool QD = qd_in_lds<S>();
   __shared__ double qd[QD ? S::N : 1];
   __shared__ unsigned int s_item;
   for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(counter, take);
+    if (threadIdx.x == 0) s_item = atomicAdd(counter, 1u);
     __syncthreads();
     // uniform across the workgroup: kept in a scalar register, so the beam's
     // arguments below are scalar loads and stay out of the vector registers
-    int64_t item = (int64_t)__builtin_amdgcn_readfirstlane(s_item);
-    const int64_t end = min(item + (int64_t)take, total);
+    const int64_t item = (int64_t)__builtin_amdgcn_readfirstlane(s_item);
     if (item >= total) break;
-    for (; item < end; ++item) {
-      __syncthreads();  // s_item is read, the item before is done with the LDS
-      int b = 0;
-      while (b + 1 < nbeams && item >= beams[b + 1].item0) ++b;
-      const BlockArgs& a = beams[b];
-      // an opaque copy of the thread index per item keeps the compiler from
+    int b = 0;
+    while (b + 1 < nbeams && item >= beams[b + 1].item0) ++b;
+    const BlockArgs& a = beams[b];
+    int64_t unit = (item - a.item0) * a.take;
+    const int64_t end = min(unit + a.take, a.units);
+    for (; unit < end; ++unit) {
+      __syncthreads();  // s_item is read, the unit before is done with the LDS
+      // an opaque copy of the thread index per unit keeps the compiler from
       // hoisting per-thread index math out of this loop (and holding it in
       // registers across it)
       int t = threadIdx.x;
       asm volatile("" : "+v"(t));
-      process_unit<S, DT, true, G>(a, item - a.item0, lds, t, QD ? qd : nullptr);
+      process_unit<S, DT, true, G>(a, unit, lds, t, QD ? qd : nullptr);
     }
   }
 }
@@ -1255,6 +1259,26 @@ static int paired_blocks(int kind, int V, const BatchBeam* beams, int nbeams, bo
   });
 }
 
+// The batch kernel of a launch and its workgroup.
+using BatchFn = void (*)(const BlockArgs*, int32_t, int64_t, unsigned int*);
+struct BatchEntry {
+  BatchFn fn = nullptr;
+  int threads = 0;
+};
+template <class S, int DT>
+static BatchEntry batch_of(bool pairs) {
+  if constexpr (tile_pairs<S>())
+    if (pairs) return {&batch_kernel<S, DT, 2>, 2 * S::T};
+  return {&batch_kernel<S, DT, wave_blocks<S>()>, S::T * wave_blocks<S>()};
+}
+static int batch_entry(const LaunchDesc& d, BatchEntry* e) {
+  return with_schedule(kLaunchBatch, d.N, d.variant, [&](auto s) {
+    using S = decltype(s);
+    *e = d.dtype == CDD_CI8 ? batch_of<S, CDD_CI8>(d.pairs) : batch_of<S, CDD_CF32>(d.pairs);
+    return 0;
+  });
+}
+
 int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int nbeams,
                    void* host_tab, LaunchDesc* d) {
   if (nbeams < 1 || !d) return (int)hipErrorInvalidValue;
@@ -1271,7 +1295,6 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
   std::vector<int> order(nbeams);
   std::vector<double> work(nbeams);
   std::vector<UnitShape> shape(nbeams);
-  double points = 0;  // of all units, per transform
   if (int err = paired_blocks(kind, out.variant, beams, nbeams, &out.pairs)) return err;
   for (int b = 0; b < nbeams; ++b) {
     const BeamPlan& p = *beams[b].p;
@@ -1292,6 +1315,22 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
     work[b] = (double)shape[b].blocks * shape[b].sets * p.N * std::log2((double)p.N) * (1 + ndm);
   }
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
+  // units of work per beam, and for the batch kernel how many of them one value
+  // of its counter stands for
+  std::vector<int64_t> units(nbeams);
+  std::vector<int32_t> take(nbeams, 1);
+  std::vector<double> points(nbeams);  // transformed per unit, all trials
+  for (int i = 0; i < nbeams; ++i) {
+    const int b = order[i];
+    units[i] = shape[b].count(beams[b].p->nchan, beams[b].co.nblocks);
+    points[i] = (double)shape[b].blocks * shape[b].sets * beams[b].p->N * (1 + beams[b].dms.ndm);
+  }
+  if (kind == kLaunchBatch) {
+    BatchEntry k;
+    int err = batch_entry(out, &k);
+    if (err || (err = resident_workgroups((const void*)k.fn, k.threads, &out.resident))) return err;
+    units_per_value(nbeams, points.data(), units.data(), out.resident, take.data());
+  }
   int64_t total = 0;
   for (int i = 0; i < nbeams; ++i) {
     const int b = order[i];
@@ -1302,59 +1341,27 @@ int prepare_launch(int kind, const BatchBeam* beams, const void* const* H, int n
                             [&](auto s) { return tables_of<decltype(s)>(ht[i]); });
     if (err) return err;
     ht[i].item0 = total;
-    const int64_t units = shape[b].count(p.nchan, beams[b].co.nblocks);
-    total += units;
-    points += (double)units * shape[b].blocks * shape[b].sets * p.N * (1 + beams[b].dms.ndm);
+    ht[i].units = units[i];
+    ht[i].take = take[i];
+    total += (units[i] + take[i] - 1) / take[i];
   }
-  if (total > (kind == kLaunchTables ? 0x7fffffffLL : 0xffffffffLL))
+  // (the persistent kernels' 32-bit counters go past the total by one per workgroup)
+  if (total > (kind == kLaunchTables ? 0x7fffffffLL : 0xffffffffLL - (1 << 20)))
     return (int)hipErrorInvalidValue;
   out.total = total;
-  out.unit_points = total > 0 ? points / (double)total : 0.0;
   *d = out;
   return 0;
 }
 
-// Units that a workgroup of the batch kernel takes from the counter at once.  The
-// counter hands out one value per 12 ns, which set the pace of short units (256
-// points, 2 trials, 512 channels x 250,000 samples: 250,000 units, 3.05 ms per
-// pass); a unit takes about 1.1 ns per point and transform.  So many are taken
-// that the counter is asked for half the values it can give, as long as each
-// workgroup still comes back four times, which keeps the end of the launch even:
-// that pass 1.20 ms, 4 trials at 512 points 2.16 -> 1.34, 2 at 1024 points 1.03 ->
-// 0.76; units of 64 trials are taken singly.
-static uint32_t units_at_once(const LaunchDesc& d, int64_t grid) {
-  const double want = std::ceil(22.0 * (double)grid / std::max(1.0, d.unit_points));
-  return (uint32_t)std::max(1.0, std::min({want, 16.0, (double)(d.total / (4 * grid))}));
-}
-
-template <class S, int DT, int G>
-static int enqueue_batch_g(const LaunchDesc& d, const void* dev_tab, unsigned int* counter,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, st, counter);
-  int64_t resident = 0;
-  int err = resident_workgroups(reinterpret_cast<const void*>(&batch_kernel<S, DT, G>), S::T * G,
-                                &resident);
+static int enqueue_batch(const LaunchDesc& d, const void* dev_tab, unsigned int* counter,
+                         hipStream_t st) {
+  BatchEntry k;
+  int err = batch_entry(d, &k);
   if (err) return err;
-  const int64_t grid = std::min<int64_t>(d.total, resident);
-  hipLaunchKernelGGL((batch_kernel<S, DT, G>), dim3((unsigned)grid), dim3(S::T * G), 0, st,
-                     (const BlockArgs*)dev_tab, d.nbeams, d.total, units_at_once(d, grid), counter);
+  hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, st, counter);
+  hipLaunchKernelGGL(k.fn, dim3((unsigned)std::min(d.total, d.resident)), dim3(k.threads), 0, st,
+                     (const BlockArgs*)dev_tab, d.nbeams, d.total, counter);
   return (int)hipGetLastError();
-}
-
-template <int N, int V, int DT>
-static int enqueue_batch_t(const LaunchDesc& d, const void* dev_tab, unsigned int* counter,
-                           hipStream_t st) {
-  using S = typename SchedFor<N, V>::type;
-  if constexpr (tile_pairs<S>())
-    if (d.pairs) return enqueue_batch_g<S, DT, 2>(d, dev_tab, counter, st);
-  return enqueue_batch_g<S, DT, wave_blocks<S>()>(d, dev_tab, counter, st);
-}
-
-template <int N, int V>
-static int enqueue_batch_dt(const LaunchDesc& d, const void* dev_tab, unsigned int* counter,
-                            hipStream_t st) {
-  return d.dtype == CDD_CI8 ? enqueue_batch_t<N, V, CDD_CI8>(d, dev_tab, counter, st)
-                            : enqueue_batch_t<N, V, CDD_CF32>(d, dev_tab, counter, st);
 }
 
 template <int N>
@@ -1414,25 +1421,7 @@ int enqueue_launch(const LaunchDesc& d, const void* host_tab, void* dev_tab,
     }
     return (int)hipErrorInvalidValue;
   }
-  switch (d.N) {
-    case 256: return enqueue_batch_dt<256, 0>(d, dev_tab, counter, st);
-    case 512: return enqueue_batch_dt<512, 0>(d, dev_tab, counter, st);
-    case 1024: return enqueue_batch_dt<1024, 0>(d, dev_tab, counter, st);
-    case 2048: return enqueue_batch_dt<2048, 0>(d, dev_tab, counter, st);
-    case 4096:
-      return d.variant == 3 ? enqueue_batch_dt<4096, 3>(d, dev_tab, counter, st)
-                            : enqueue_batch_dt<4096, 0>(d, dev_tab, counter, st);
-    case 8192:
-      switch (d.variant) {
-        case 1: return enqueue_batch_dt<8192, 1>(d, dev_tab, counter, st);
-        case 2: return enqueue_batch_dt<8192, 2>(d, dev_tab, counter, st);
-        default: return enqueue_batch_dt<8192, 0>(d, dev_tab, counter, st);
-      }
-    case 16384:
-      return d.variant == 2 ? enqueue_batch_dt<16384, 2>(d, dev_tab, counter, st)
-                            : enqueue_batch_dt<16384, 0>(d, dev_tab, counter, st);
-  }
-  return (int)hipErrorInvalidValue;
+  return enqueue_batch(d, dev_tab, counter, st);
 }
 
 int launch_batch(const BatchBeam* beams, int nbeams, void* host_tab, void* dev_tab,

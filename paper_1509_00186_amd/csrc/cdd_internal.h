@@ -159,8 +159,8 @@ enum { kLaunchMixed = 0, kLaunchTables = 1, kLaunchBatch = 2 };
 struct LaunchDesc {
   int kind = 0, N = 0, variant = 0, nbeams = 0, multi = 0, dtype = 0;
   bool pairs = false; // batch launches: two blocks of a channel per unit
-  int64_t total = 0;  // work units
-  double unit_points = 0;  // points transformed per unit of work (mean), all trials
+  int64_t total = 0;  // work units (batch launches: values of the counter)
+  int64_t resident = 0;  // batch launches: workgroups that fit on the device at once
 };
 // The schedule (variant of its length) that a launch runs, and so reads a chirp
 // table of; V is the beam's own.

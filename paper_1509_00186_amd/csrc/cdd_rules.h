@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 namespace cdd {
@@ -35,6 +36,28 @@ inline bool two_blocks_pay(int N, double trials, int64_t blocks, int64_t doubled
                              : 1.19 + 1.0 / trials;
   limit = std::min(limit, 4.0 / 3.0);
   return (double)doubled <= limit * (double)blocks * (1.0 + 1e-12);
+}
+
+// Units of work that one value of the batch kernel's counter stands for, per beam of
+// a launch (listed longest unit first; points: transformed per unit, all trials).
+// The counter hands out one value per 12 ns, which set the pace of short units (256
+// points, 2 trials, 512 channels x 250,000 samples: 250,000 units, 3.05 ms per pass);
+// a unit takes about 1.1 ns per point.  So many are taken that the counter is asked
+// for half the values it can give (22 points per resident workgroup and value), as
+// long as each workgroup comes back four times from there to the end of the launch,
+// which keeps the end even: that pass 1.20 ms, 4 trials at 512 points 2.16 -> 1.34,
+// 2 at 1024 points 1.03 -> 0.76.  Units of 64 trials are taken singly, also beside
+// beams of many short units.
+inline void units_per_value(int n, const double* points, const int64_t* units, int64_t resident,
+                            int32_t* take) {
+  int64_t left = 0;
+  for (int i = 0; i < n; ++i) left += units[i];
+  const int64_t grid = std::max<int64_t>(1, std::min(left, resident));
+  for (int i = 0; i < n; ++i) {
+    const double want = std::ceil(22.0 * (double)grid / std::max(1.0, points[i]));
+    take[i] = (int32_t)std::max(1.0, std::min({want, 16.0, (double)(left / (4 * grid))}));
+    left -= units[i];
+  }
 }
 
 // Whether the incoherent path detects straight from the time-major record or from

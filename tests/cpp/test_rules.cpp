@@ -70,8 +70,35 @@ static void test_fold() {
   CHECK(fold_threads(1000, 1.5, 8193) == 1);
 }
 
+// Each beam's units are taken by their own length.
+static void test_units_per_value() {
+  int32_t take[2];
+  // 64 trials at 2048 points beside 2 trials of many blocks at the same length
+  const double points[] = {2048.0 * 65, 2048.0 * 3};
+  const int64_t units[] = {5000, 400000};
+  units_per_value(2, points, units, 1024, take);
+  CHECK(take[0] == 1 && take[1] == 4);
+  const double small[] = {256.0 * 4 * 65, 256.0 * 4 * 3};
+  units_per_value(2, small, units, 2048, take);
+  CHECK(take[0] == 1 && take[1] == 15);
+  // short units alone: at most 16 at once, and four values per workgroup to the end
+  for (int64_t n : {1, 100, 2048, 8191, 8192, 40000, 250000, 100000000}) {
+    const double p = 256.0 * 3;
+    units_per_value(1, &p, &n, 2048, take);
+    CHECK(take[0] >= 1 && take[0] <= 16);
+    CHECK(take[0] == 1 || n / take[0] >= 4 * 2048);
+    CHECK(n < 250000 || take[0] == 16);
+  }
+  // the last beam of a launch is handed out evenly, however many went before
+  const double same[] = {768.0, 768.0};
+  const int64_t tail[] = {1000000, 3000};
+  units_per_value(2, same, tail, 2048, take);
+  CHECK(take[0] == 16 && take[1] == 1);
+}
+
 int main() {
   test_two_blocks();
+  test_units_per_value();
   test_fold();
   test_detection();
   if (g_fail) {
