@@ -60,7 +60,7 @@ template <> struct SchedFor<8192, 2> { using type = Sched<8192, 512, 16, 16, 16,
 template <> struct SchedFor<8192, 3> { using type = Sched<8192, 512, 16, 16, 16, 2, false, true, 4>; };
 template <> struct SchedFor<8192, 4> { using type = Sched<8192, 256, 32, 16, 16, 1, true, true, 3>; };
 template <> struct SchedFor<8192, 5> { using type = Sched<8192, 256, 16, 32, 16, 1, true, true, 3>; };
-template <> struct SchedFor<8192, 6> { using type = Sched<8192, 256, 16, 16, 32, 1, true, true, 3>; };
+template <> struct SchedFor<8192, 6> { using type = Sched<8192, 256, 16, 16, 32, 1, true, false, 3>; };
 template <> struct SchedFor<8192, 7> { using type = Sched<8192, 256, 16, 16, 32, 1, true, true, 2>; };
 template <> struct SchedFor<8192, 8> { using type = Sched<8192, 256, 16, 16, 32, 1, true, false, 4>; };
 template <> struct SchedFor<8192, 9> { using type = Sched<8192, 128, 16, 16, 32, 1, true, false, 2>; };
@@ -69,6 +69,21 @@ template <> struct SchedFor<16384, 1> { using type = Sched<16384, 512, 16, 32, 3
 template <> struct SchedFor<16384, 2> { using type = Sched<16384, 1024, 16, 16, 16, 4, true, false, 4>; };
 template <> struct SchedFor<16384, 3> { using type = Sched<16384, 512, 32, 32, 16, 1, true, true, 2>; };
 constexpr int kVariants[] = {1, 1, 1, 1, 4, 10, 4};  // per log2(N) - 8
+
+// No two variants of a length are the same schedule.
+template <int N, int V, int... I>
+constexpr bool differs_from_later(std::integer_sequence<int, I...>) {
+  return (true && ... &&
+          (I <= V || !std::is_same_v<typename SchedFor<N, V>::type, typename SchedFor<N, I>::type>));
+}
+template <int N, int... V>
+constexpr bool variants_differ(std::integer_sequence<int, V...> all) {
+  return (true && ... && differs_from_later<N, V>(all));
+}
+static_assert(variants_differ<4096>(std::make_integer_sequence<int, kVariants[4]>()) &&
+                  variants_differ<8192>(std::make_integer_sequence<int, kVariants[5]>()) &&
+                  variants_differ<16384>(std::make_integer_sequence<int, kVariants[6]>()),
+              "variants of a length");
 
 // ---------------------------------------------------------------------------
 // Kernel
