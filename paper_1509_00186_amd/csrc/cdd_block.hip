@@ -48,8 +48,8 @@ template <int N, int V>
 struct SchedFor;
 template <> struct SchedFor<256, 0> { using type = Sched<256, 16, 16, 16, 1, 1, true, true>; };
 template <> struct SchedFor<512, 0> { using type = Sched<512, 64, 8, 8, 8, 1>; };
-template <> struct SchedFor<1024, 0> { using type = Sched<1024, 64, 16, 16, 4, 1, true, true>; };
-template <> struct SchedFor<2048, 0> { using type = Sched<2048, 128, 16, 16, 8, 1, true, true>; };
+template <> struct SchedFor<1024, 0> { using type = Sched<1024, 64, 16, 16, 4, 1>; };
+template <> struct SchedFor<2048, 0> { using type = Sched<2048, 128, 16, 16, 8, 1>; };
 template <> struct SchedFor<4096, 0> { using type = Sched<4096, 128, 16, 16, 16, 1, true, true, 3>; };
 template <> struct SchedFor<4096, 1> { using type = Sched<4096, 256, 16, 16, 16, 1, false, false, 2>; };
 template <> struct SchedFor<4096, 2> { using type = Sched<4096, 256, 16, 16, 16, 1, true, true, 3>; };
@@ -635,6 +635,18 @@ constexpr int wg_waves() {  // waves per SIMD the register budget targets
   return G > wave_blocks<S>() && S::E <= 16 ? 4 : (S::MINB + 1) / 2;
 }
 
+// The form of schedule S that DM tiles run: at 1024 and 2048 points with the twiddles
+// loaded ahead of the exchange (64 trials at 2048 points 11.52 -> 11.43 ms).  With one
+// DM that saves as little of a full launch (four beams 2.86 -> 2.84 ms) but adds a
+// microsecond to the only wave of a short one (2 channels at 1024 points 17.8 -> 19.3
+// us a call, 16 at 2048 points 21.4 -> 22.7).
+template <class S>
+struct EarlyTwiddles : S {
+  static constexpr bool PF = true;
+};
+template <class S>
+using TileForm = std::conditional_t<S::N == 1024 || S::N == 2048, EarlyTwiddles<S>, S>;
+
 // Unit of work `unit` of beam a: blocks kg G .. kg G + G - 1 of one channel.
 // The last unit of a channel may hold fewer; its spare groups run on the last
 // block without storing anything (they keep the workgroup's barriers in step).
@@ -706,7 +718,7 @@ __global__ __launch_bounds__(S::T * G, (wg_waves<S, true, G>())) void batch_kern
       // registers across it)
       int t = threadIdx.x;
       asm volatile("" : "+v"(t));
-      process_unit<S, DT, true, G>(a, unit, lds, t, QD ? qd : nullptr);
+      process_unit<TileForm<S>, DT, true, G>(a, unit, lds, t, QD ? qd : nullptr);
     }
   }
 }
