@@ -26,6 +26,7 @@ import hashlib
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -60,11 +61,25 @@ def flops_per_output_sample(N: int, M: int) -> float:
     return (10.0 * math.log2(N) + 6.0) * N / M + 4.0
 
 
-def source_digest(files=("cdd_block.hip", "cdd_fft.h", "cdd_internal.h")) -> str:
+CSRC = os.path.join(ROOT, "paper_1509_00186_amd", "csrc")
+
+
+def kernel_sources(source: str):
+    """A kernel's source file and the library's headers that it includes,
+    directly or through others."""
+    files = [source]
+    for f in files:
+        with open(os.path.join(CSRC, f)) as fh:
+            files += [h for h in re.findall(r'^#include "(cdd_\w+\.h)"', fh.read(), re.M)
+                      if h not in files]
+    return files
+
+
+def source_digest(files) -> str:
     """Digest of the sources a kernel is compiled from."""
     h = hashlib.sha256()
     for f in files:
-        with open(os.path.join(ROOT, "paper_1509_00186_amd", "csrc", f), "rb") as fh:
+        with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
@@ -78,8 +93,7 @@ def measured_traffic(kernel: str, workload: str):
         rec = data[kernel][workload]
     except Exception:
         return None
-    files = rec.get("sources", ["cdd_block.hip", "cdd_fft.h", "cdd_internal.h"])
-    if rec.get("source_digest") != source_digest(files):
+    if rec.get("source_digest") != source_digest(kernel_sources(rec["sources"][0])):
         return None
     return rec.get("bytes_per_launch")
 
