@@ -313,10 +313,6 @@ __device__ __forceinline__ void chirp_from_table(float2* v, const float2* h, int
   }
 }
 
-// Load block k = kw + dk of channel c (kw: the wave's first block): sample n of
-// the block is input sample k*M - load_off + n, zero outside [0, x_len).  Blocks that start inside the
-// data read through a buffer resource whose range ends at the data's end, so
-// the hardware returns zeros past it and no per-sample test is needed.
 // Blocks in a wave.  They belong to one channel, so that the buffer resources of
 // its samples and chirp row are uniform in the wave.
 template <class S>
@@ -324,6 +320,11 @@ constexpr int wave_blocks() {
   return S::T < 64 ? 64 / S::T : 1;
 }
 
+// Load block k = kw + dk of channel c (kw: the wave's first block): sample n of
+// the block is input sample k*M - load_off + n, zero outside [0, x_len).  Blocks
+// that start inside the data read through a buffer resource whose range ends at
+// the data's end, so the hardware returns zeros past it and no per-sample test is
+// needed.
 template <class S, int DT>
 __device__ __forceinline__ void load_block(float2* v, const BlockArgs& a, int c, int64_t kw, int dk,
                                            int t) {
@@ -528,7 +529,7 @@ __device__ __forceinline__ void process_item(const BlockArgs& a, int c, int64_t 
   // holds registers
   const bool stepped = MULTI && qd != nullptr && a.phase_mode == CDD_PHASE_FP64_REDUCED &&
                        a.dm_step != 0.0;
-  if (stepped) 
+  if (stepped)
     rotation_table<S>(reinterpret_cast<float2*>(qd), a.dms.dm[0], a.first, fc, a, t, g, ng);
   float2 v[S::E];
   if constexpr (DT == CDD_CI8 && mf_schedule<S>()) {
