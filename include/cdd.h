@@ -449,7 +449,8 @@ typedef struct {
 
 /* Create a server on the current device.  ENOMEM, EDEVICE. */
 cdd_status cdd_server_create(const cdd_server_opts* opts, cdd_server** out);
-/* Finish all queued work, then free everything. */
+/* Wait for pushes under way in other threads (later ones are refused), finish
+ * all queued work, then free everything. */
 void cdd_server_destroy(cdd_server* server);
 /* Admit a stream (plan as cdd_query with nsamp = max_block).  EAGAIN when
  * its device memory would exceed the budget or all slots are taken; EINVAL
@@ -467,8 +468,8 @@ cdd_status cdd_stream_open(cdd_server* server, const cdd_stream_desc* desc,
  * are reported by cdd_stream_invalid (the paper's real-time check is that
  * no block is lost, Sec. 4.5).  EAGAIN when queue_depth blocks are already
  * waiting (retry later); EINVAL for nsamp < 1 or > max_block (or >
- * block_len, or any push after one shorter than block_len), or a closed
- * stream. */
+ * block_len, or any push after one shorter than block_len), a closed
+ * stream, or a server that is being destroyed. */
 cdd_status cdd_stream_push(cdd_server* server, int32_t stream_id,
                            const void* host_block, int64_t nsamp, uint64_t seq);
 /* Copy up to cap finished samples of the stream's aligned sum I[u] (FP32,
@@ -490,7 +491,8 @@ cdd_status cdd_stream_invalid(cdd_server* server, int32_t stream_id, int64_t* sp
  * the end, as cdd_dedisperse).  The stream's memory is returned to the
  * budget once its last sample has been polled. */
 cdd_status cdd_stream_close(cdd_server* server, int32_t stream_id);
-/* Wait until every pushed block is finished. */
+/* Wait until every pushed block is finished, those included that a push under
+ * way in another thread has claimed a slot for. */
 cdd_status cdd_server_sync(cdd_server* server);
 cdd_status cdd_server_stats_get(cdd_server* server, cdd_server_stats* out);
 

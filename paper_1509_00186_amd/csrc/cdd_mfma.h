@@ -9,7 +9,9 @@
 // to lie close to pairs: the largest error is 1.4e-9, every entry at or below that of
 // its FP32 number, and none of the parts is a subnormal.  (Three halves without a
 // scale: 512 channels 413 -> 428 us.)  The scale is taken out by the chirp, with the
-// 1/N of the inverse transform.  The products accumulate in FP32.  The pass takes three vector operations per sample (byte pair to halves) where the
+// 1/N of the inverse transform.  The products accumulate in FP32.
+//
+// The pass takes three vector operations per sample (byte pair to halves) where the
 // conversion and the radix-16 butterfly took 14, and the matrix cores, idle
 // otherwise, work beside the vector ALU, which bounds these kernels.  The later
 // passes stay on the vector ALU: their FP32 values would have to be split into
